@@ -138,11 +138,18 @@ __host__ __device__ constexpr int up_lds_bytes(int M, int TM) { return 2 * (TM +
 __host__ __device__ constexpr int down_lds_bytes(int TM, int BN) { return 2 * (TM + BN) * Stage::RB + 16 * TM + 16; }
 
 // Per-XCD tile queue: XCD x (= blockIdx.x % 8) owns tiles [lo, hi) of the
-// table and hands them out in order through counter queue[x]. Indices past
-// hi mean "no tile". gridDim.x is a multiple of kXcds.
+// table. Its g = gridDim.x / 8 workgroups start with tiles lo .. lo + g - 1,
+// one each by their index, and take the rest in order through counter
+// queue[x]. (Taking the first two tiles from the counter left half of the
+// compute units idle when a call has fewer tiles than twice the workgroups,
+// and put the atomic's round trip before the first copy.) Indices past hi
+// mean "no tile". gridDim.x is a multiple of kXcds.
 struct TileQueue {
     int* ctr;
     int lo, hi;
+    __device__ int first() const { return lo + (int)(blockIdx.x / kXcds); }
+    // The tile of a taken ticket.
+    __device__ int at(int ticket) const { return lo + (int)(gridDim.x / kXcds) + ticket; }
     __device__ TileQueue(int* queue, int n_tiles) {
         const int x = blockIdx.x % kXcds;
         ctr = queue + x;
@@ -156,9 +163,8 @@ struct TileQueue {
         lo = ld_uniform(slices + x);
         hi = ld_uniform(slices + x + 1);
     }
-    // One lane only (a vector atomic with return); the result is an offset
-    // from lo.
-    __device__ int take(int n) const { return atomicAdd(ctr, n); }
+    // The next ticket; one lane only (a vector atomic with return).
+    __device__ int take() const { return atomicAdd(ctr, 1); }
 };
 
 // Wait until at most n vector-memory operations of this wave are pending,
@@ -230,19 +236,14 @@ void up_kernel(UpParams p) {
     const int nk = p.d / S::SK;                       // real stages per tile
     const int nst = max(nk, 4);                       // stages per tile, padding included
     const TileQueue tq(p.queue, n_tiles);
-    // ctl[0], ctl[1]: the first two tiles; ctl[2]: the tile after next,
+    // ctl[0]: the ticket of the second tile, taken here and read once the
+    // first tile's row lists are in; ctl[1]: that of the tile after next,
     // taken at stage 0 of each tile, written at stage 1, read after stage 2.
     int* ctl = reinterpret_cast<int*>(lds_up + RING + 16 * TM);
-    if (tid == 0) {
-        const int t = tq.take(2);
-        ctl[0] = t;
-        ctl[1] = t + 1;
-    }
-    __syncthreads();
-    int tile = tq.lo + __builtin_amdgcn_readfirstlane(ctl[0]);
-    int next = tq.lo + __builtin_amdgcn_readfirstlane(ctl[1]);
+    int tile = tq.first();
     if (tile >= tq.hi) return;
     int taken = 0;
+    if (tid == 0) taken = tq.take();
 
     // Fragment addresses inside a stage: lane (lr, lh) reads row base + lr,
     // chunk 2 k + lh of k step k; 32-row steps keep the swizzle, so row
@@ -318,8 +319,10 @@ void up_kernel(UpParams p) {
     int par = 0;
     int info = ld_uniform(p.tile_info + tile);
     fetch_rows(ld_uniform(p.tile_rows + tile), 0);
+    if (tid == 0) ctl[0] = taken;
     wait_vmcnt<0>();
     __syncthreads();
+    int next = tq.at(__builtin_amdgcn_readfirstlane(ctl[0]));
     sources(0, info);
 #pragma unroll
     for (int st = 0; st < 2; ++st) {
@@ -384,8 +387,8 @@ void up_kernel(UpParams p) {
             __builtin_amdgcn_s_barrier();
             // The atomic is issued before stage s + 2's copies, so the wait
             // of stage 1 (for stage 2) covers it.
-            if (s == 0 && has_next && tid == 0) taken = tq.take(1);
-            if (s == 1 && has_next && tid == 0) ctl[2] = taken;
+            if (s == 0 && has_next && tid == 0) taken = tq.take();
+            if (s == 1 && has_next && tid == 0) ctl[1] = taken;
             if (s + 2 == nst) {
                 // The stages issued from here on belong to the next tile, or,
                 // past the last tile, re-read this tile's first ones.
@@ -510,7 +513,7 @@ void up_kernel(UpParams p) {
         }
         if (!has_next) break;
         tile = next;
-        next = tq.lo + __builtin_amdgcn_readfirstlane(ctl[2]);
+        next = tq.at(__builtin_amdgcn_readfirstlane(ctl[1]));
         info = next_info;
         par ^= 1;
         after_epi = true;
@@ -557,16 +560,10 @@ void down_kernel(DownParams p) {
     const TileQueue tq(p.queue, p.slices);
     // ctl as in the up kernel.
     int* ctl = reinterpret_cast<int*>(lds_dn + RING + 16 * TM);
-    if (tid == 0) {
-        const int t = tq.take(2);
-        ctl[0] = t;
-        ctl[1] = t + 1;
-    }
-    __syncthreads();
-    int tile = tq.lo + __builtin_amdgcn_readfirstlane(ctl[0]);
-    int next = tq.lo + __builtin_amdgcn_readfirstlane(ctl[1]);
+    int tile = tq.first();
     if (tile >= tq.hi) return;
     int taken = 0;
+    if (tid == 0) taken = tq.take();
 
     const int lr = lane & 31, lh = lane >> 5;
     uint32_t fx[KS], fw[KS];
@@ -702,8 +699,10 @@ void down_kernel(DownParams p) {
     int par = 0;
     Desc cur = describe(tile);
     fetch_masks(cur, 0);
+    if (tid == 0) ctl[0] = taken;
     wait_vmcnt<0>();
     __syncthreads();
+    int next = tq.at(__builtin_amdgcn_readfirstlane(ctl[0]));
     issue_tile(cur, 0);
 #pragma unroll
     for (int st = 0; st < 2; ++st) {
@@ -771,8 +770,8 @@ void down_kernel(DownParams p) {
             wait_lgkmcnt0();
             wait_stage<NEPI, NFETCH>(s, after_epi, has_next);
             __builtin_amdgcn_s_barrier();
-            if (s == 0 && has_next && tid == 0) taken = tq.take(1);
-            if (s == 1 && has_next && tid == 0) ctl[2] = taken;
+            if (s == 0 && has_next && tid == 0) taken = tq.take();
+            if (s == 1 && has_next && tid == 0) ctl[1] = taken;
             if (s + 2 == nst) {
                 // The stages issued from here on belong to the next tile (or,
                 // past the last tile, re-read this tile's first stages). Its
@@ -812,7 +811,7 @@ void down_kernel(DownParams p) {
         }
         if (!has_next) break;
         tile = next;
-        next = tq.lo + __builtin_amdgcn_readfirstlane(ctl[2]);
+        next = tq.at(__builtin_amdgcn_readfirstlane(ctl[1]));
         cur = nxt;
         par ^= 1;
         after_epi = true;
