@@ -43,6 +43,9 @@ __device__ __forceinline__ u16 f2bf(float f) {
 
 __device__ __forceinline__ u32x4 ld16(const void* p) { return *reinterpret_cast<const u32x4*>(p); }
 __device__ __forceinline__ void st16(void* p, u32x4 v) { *reinterpret_cast<u32x4*>(p) = v; }
+// Four consecutive floats at any 4-byte aligned address.
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ f32x4 ld_f32x4(const float* p) { return *reinterpret_cast<const f32x4_a4*>(p); }
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
 // D = A(16x32) * B(32x16) + C on the matrix cores. Lane l supplies row

@@ -1,33 +1,35 @@
-// Fused routing kernel (Sec. III-B and III-C): router logits, shared demand,
-// shared block count and prototype selection, residual softmax, sort,
-// cumulative-mass expert count, and the per-tile counts that the
-// permutation needs.
+// Routing (Sec. III-B and III-C): router logits, shared demand, shared block
+// count and prototype selection, residual softmax, sort, cumulative-mass
+// expert count, and the per-tile counts that the permutation needs.
 //
-// Phase 1 computes the 1 + K + B logits of each token (x W_shr, x W_1..x W_K,
-// x mu_1..x mu_B) into LDS:
+// Logits, 1 + K + B per token (x W_shr, x W_1..x W_K, x mu_1..x mu_B):
 //   * bf16 tokens: x W_1.., x mu_1.. on the matrix cores. The fp32 router
 //     and prototype weights are pre-split into three bf16 parts (hi + mid +
 //     lo carries all 24 significand bits), so every bf16 x bf16 product is
 //     exact and only the fp32 accumulation order differs from a sequential
 //     dot product. x W_shr is an fp32 dot product on the vector units.
-//   * fp32 tokens: sequential fp32 FMA dot products.
-// Phase 2 decides each token with a group of 16, 32 or 64 lanes (one lane
-// per expert and per block) using wave-level exchanges: a butterfly maximum
-// and index-order broadcast sums for the softmax, broadcast comparisons for
-// the rankings (ties toward the lower index), a lane permute for the sort
-// and an in-order prefix with a ballot for the cumulative-mass count. Every
-// step is the paper's order in fp32 with explicitly rounded operations.
-// Per tile of 64 tokens, the rows per (expert, block) slab and the pairs per
-// expert are counted in LDS and written out for the permutation.
+//   * fp32 tokens: the matrix cores in fp32 (v_mfma_f32_16x16x4_f32).
+// Decisions: one wave per tile of 64 tokens, one lane per token (decide_tile).
+// Every step is the paper's order in fp32 with explicitly rounded operations;
+// the rankings (ties toward the lower index) are sorting networks in the
+// lane's registers. Per tile, the rows per (expert, block) slab and the pairs
+// per expert are counted for the permutation.
+//
+// Three launches share the work by size (launch_route):
+//   route_logits_kernel + route_decide_kernel   routers of at most 32 columns,
+//                   d <= 1024: the router stays in registers
+//   route_wide_kernel    wider bf16 routers, many tokens: one tile per wave,
+//                   the router streams through LDS for four tiles at once
+//   route_split_k_kernel few tokens, or fp32: one tile per workgroup, its
+//                   waves share the contraction
 #pragma once
 #include "common.hpp"
 
 namespace unifmoe {
 
-constexpr int kRouteTok = 128;
-// 4 waves: in the logits, wave w takes tokens 64 (w & 1).. and half (w >> 1)
-// of the k range; then all four share each tile's decisions.
-constexpr int kRouteThreads = 256;
+// Tokens are routed in tiles of kTileTok (a wave's lanes); the permutation's
+// per-tile counts use the same tiles.
+constexpr int kTileTok = 64;
 
 struct RouteParams {
     int N, d, K, B, NL, NLP, lstride, key_bits;
@@ -37,7 +39,7 @@ struct RouteParams {
     const uint8_t* valid;
     const float* Wr;    // fp32 logits: [K+1][d]
     const float* mu;    // fp32 logits: [B][d]
-    const u16* Wsplit;  // bf16 logits: [3][NLP][d], rows W_1..W_K, mu_1..mu_B, 0...
+    const u16* Wsplit;  // bf16 logits: the router's three parts (split_at), rows W_1..W_K, mu_1..mu_B, 0...
     float* alpha;
     int* nsh;
     uint64_t* mask;
@@ -94,6 +96,13 @@ __device__ __forceinline__ bool route_copy_role(const RouteParams& p) {
     return true;
 }
 
+// Place of element k of row `row` of part `part` in the split router: blocks
+// of 64 k, each holding all 3 NLP rows as 128-byte lines, so that what a k
+// step reads is one contiguous stretch, whatever d.
+__host__ __device__ __forceinline__ size_t split_at(int NLP, int part, int row, int k) {
+    return ((size_t)(k >> 6) * 3 * NLP + (size_t)part * NLP + row) * 64 + (k & 63);
+}
+
 // Exact three-way split of an fp32 value into bf16 parts, in workgroups
 // [0, nsplit); the workgroups after them zero zwords words at zero (the
 // forward's counters, in the same launch).
@@ -117,139 +126,9 @@ __global__ void split_router_kernel(const float* __restrict__ Wr, const float* _
     const float r1 = w - bf2f(hi);
     const u16 mid = f2bf(r1);
     const float r2 = r1 - bf2f(mid);
-    out[i] = hi;
-    out[total + i] = mid;
-    out[2 * total + i] = f2bf(r2);
-}
-
-// Logits of the bf16 path. Each wave takes 64 tokens (four 16-row MFMA
-// fragments), so every weight fragment it loads serves four MFMAs.
-//  * The K + B expert and prototype logits run on the matrix cores in NCT
-//    16-column tiles, three exact bf16 parts per weight.
-//  * The shared-demand logit x W_shr is a plain fp32 dot product on the
-//    vector units, in the shadow of the MFMAs: each lane sums its 8 k of
-//    every k step, then the four lane groups of a row are added.
-// Every operand of a k step is loaded together, D - 1 k steps ahead of its
-// use, so the loads overlap each other and the MFMAs of earlier steps.
-template <int NCT>
-__device__ __forceinline__ void route_logits_bf16(const RouteParams& p, float* L, int tok0) {
-    constexpr int RT = 4;                    // 16-row fragments per wave
-    constexpr int D = (NCT <= 2) ? 3 : 2;    // register sets in the ring
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int w = wave & 1, kh = wave >> 1;  // token half, k half
-    const u16* X = static_cast<const u16*>(p.X);
-    f32x4 acc[RT][NCT];
-    float sh[RT];
-#pragma unroll
-    for (int i = 0; i < RT; ++i) {
-        sh[i] = 0.f;
-#pragma unroll
-        for (int j = 0; j < NCT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    const int kof = (lane >> 4) * 8;
-    const u16* xr[RT];
-#pragma unroll
-    for (int i = 0; i < RT; ++i) {
-        // Rows past N read row N - 1; their logits are never used.
-        const int r = min(tok0 + w * 64 + i * 16 + (lane & 15), p.N - 1);
-        xr[i] = X + (size_t)r * p.d + kof;
-    }
-    const u16* wb = p.Wsplit + (size_t)(lane & 15) * p.d + kof;
-    const float* wsh = p.Wr + kof;           // row 0 of the fp32 router: W_shr
-    const size_t part_stride = (size_t)p.NLP * p.d, ct_stride = (size_t)16 * p.d;
-    const int nks_all = p.d / 32;
-    const int ks0 = kh ? nks_all / 2 : 0;
-    const int nks = kh ? nks_all - nks_all / 2 : nks_all / 2;
-    struct Set {
-        u32x4 a[RT], b[3][NCT], s0, s1;
-    };
-    Set ring[D];
-    auto load = [&](int ks, Set& S) {
-        const int k0 = (ks0 + ks) * 32;
-#pragma unroll
-        for (int i = 0; i < RT; ++i) S.a[i] = ld16(xr[i] + k0);
-#pragma unroll
-        for (int part = 0; part < 3; ++part)
-#pragma unroll
-            for (int ct = 0; ct < NCT; ++ct) S.b[part][ct] = ld16(wb + part * part_stride + ct * ct_stride + k0);
-        S.s0 = ld16(wsh + k0);
-        S.s1 = ld16(wsh + k0 + 4);
-    };
-    auto compute = [&](const Set& S) {
-#pragma unroll
-        for (int ct = 0; ct < NCT; ++ct)
-#pragma unroll
-            for (int part = 0; part < 3; ++part) {
-                const bf16x8 b = as_bf16x8(S.b[part][ct]);
-#pragma unroll
-                for (int i = 0; i < RT; ++i) acc[i][ct] = mfma16x16x32(as_bf16x8(S.a[i]), b, acc[i][ct]);
-            }
-#pragma unroll
-        for (int i = 0; i < RT; ++i) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const uint32_t u = S.a[i][q];
-                sh[i] = fmaf(__uint_as_float(u << 16), __uint_as_float(q < 2 ? S.s0[2 * q] : S.s1[2 * q - 4]), sh[i]);
-                sh[i] = fmaf(__uint_as_float(u & 0xffff0000u),
-                             __uint_as_float(q < 2 ? S.s0[2 * q + 1] : S.s1[2 * q - 3]), sh[i]);
-            }
-        }
-    };
-#pragma unroll
-    for (int i = 0; i < D - 1; ++i)
-        if (i < nks) load(i, ring[i]);
-    for (int ks = 0; ks < nks; ks += D) {
-#pragma unroll
-        for (int i = 0; i < D; ++i) {
-            if (ks + i < nks) {
-                if (ks + i + D - 1 < nks) load(ks + i + D - 1, ring[(i + D - 1) % D]);
-                compute(ring[i]);
-            }
-        }
-    }
-    // Column 0: the shared-demand logit; columns 1..: the MFMA tiles. The
-    // second k half is written first; the first adds it to its own sums
-    // (same order for every token).
-#pragma unroll
-    for (int i = 0; i < RT; ++i) {
-        float v = sh[i];
-        v += __shfl_xor(v, 16);
-        v += __shfl_xor(v, 32);
-        sh[i] = v;
-    }
-    for (int half = 1; half >= 0; --half) {
-        if (kh == half) {
-#pragma unroll
-            for (int i = 0; i < RT; ++i) {
-                float* row0 = L + (size_t)(w * 64 + i * 16) * p.lstride;
-                if (lane < 16) {
-                    float* d0 = row0 + lane * p.lstride;
-                    *d0 = half ? sh[i] : sh[i] + *d0;
-                }
-#pragma unroll
-                for (int ct = 0; ct < NCT; ++ct)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        float* d = row0 + ((lane >> 4) * 4 + r) * p.lstride + 1 + ct * 16 + (lane & 15);
-                        *d = half ? acc[i][ct][r] : acc[i][ct][r] + *d;
-                    }
-            }
-        }
-        __syncthreads();
-    }
-}
-
-__device__ __forceinline__ void route_logits_f32(const RouteParams& p, float* L, int tok0) {
-    const float* X = static_cast<const float*>(p.X);
-    for (int idx = threadIdx.x; idx < kRouteTok * p.NL; idx += blockDim.x) {
-        const int t = idx / p.NL, j = idx - (idx / p.NL) * p.NL, tok = tok0 + t;
-        if (tok >= p.N) continue;
-        const float* w = (j <= p.K) ? p.Wr + (size_t)j * p.d : p.mu + (size_t)(j - 1 - p.K) * p.d;
-        const float* x = X + (size_t)tok * p.d;
-        float s = 0.f;
-        for (int i = 0; i < p.d; ++i) s = fmaf(x[i], w[i], s);
-        L[t * p.lstride + j] = s;
-    }
+    out[split_at(NLP, 0, j, k)] = hi;
+    out[split_at(NLP, 1, j, k)] = mid;
+    out[split_at(NLP, 2, j, k)] = f2bf(r2);
 }
 
 // Total-order key of a float for ranking: for non-NaN values it orders as
@@ -261,45 +140,109 @@ __device__ __forceinline__ uint32_t rank_key(float f) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// Tokens are decided in tiles of kTileTok (one wave's ballot); the
-// permutation's per-tile counts use the same tiles.
-constexpr int kTileTok = 64;
-
-// Lanes per token in the decisions: the smallest power of two >= max(K, B),
-// at least 16.
-__host__ __device__ __forceinline__ int decide_lanes(int K, int B) {
-    const int n = K > B ? K : B;
-    return n <= 16 ? 16 : (n <= 32 ? 32 : 64);
+// Entry c of a list of L as one number that orders by (value descending,
+// index ascending) under > : the value's rank_key in the top 32 mantissa
+// bits of a double, L - 1 - c in the low ones. All entries share one binade
+// (exponent field 1), so they compare as integers do, as finite normal
+// numbers, and a compare-exchange is one v_max_f64 and one v_min_f64. 0.0
+// comes after every entry.
+template <int L>
+__device__ __forceinline__ double order_key(float f, int c) {
+    const uint32_t r = rank_key(f);
+    return __hiloint2double((int)(0x00100000u | (r >> 12)), (int)((r << 20) | (uint32_t)(L - 1 - c)));
+}
+// The value's rank_key and the index of an order_key.
+__device__ __forceinline__ uint32_t order_value(double k) {
+    return ((uint32_t)__double2hiint(k) << 12) | ((uint32_t)__double2loint(k) >> 20);
+}
+template <int L>
+__device__ __forceinline__ int order_index(double k) {
+    return (L - 1) - (int)((uint32_t)__double2loint(k) & (L - 1));
 }
 
-// Decisions of Sec. III-B and III-C for 64 / L tokens of one tile per call,
-// L lanes per token (lane j of a token's group stands for expert j + 1 and
-// block j), with wave-level exchanges instead of per-token loops:
-//   alpha, b          every lane of the group, from the shared logit
-//   I_shr             lane c ranks x mu_c against the other B priorities
-//                     (broadcasts in index order, ties to the lower index)
-//   softmax           group maximum (butterfly), then the sum of the
-//                     exponentials in index order (broadcasts), fp32
-//   q, p              lane j ranks s_j; a permute sends (s_j, j + 1) to lane
-//                     rank(j), so lane r then holds p_r and q_r
-//   P_r, k            lane r sums p_0..p_r in order; k is the first lane
-//                     whose prefix reaches the target (ballot), else K
-// All arithmetic is the paper's order in fp32 with explicitly rounded
-// operations. `row` is the token's logit row in LDS (shared logit, K expert
-// logits, B priorities); `t` the token's index in the tile (tokens at or past
-// `ntok` are outside the layer and write nothing); `cnt` the tile's LDS
-// counters (rows per (expert, block) slab, then pairs per expert), or null.
+// Batcher's odd-even merge sort of a[LO .. LO + N), largest first (N a power
+// of two): 19, 63, 191 and 543 compare-exchanges for 8, 16, 32 and 64.
+__device__ __forceinline__ void order_pair(double& a, double& b) {
+    const double x = __builtin_fmax(a, b), y = __builtin_fmin(a, b);
+    a = x;
+    b = y;
+}
+template <int LO, int N, int R, int L>
+__device__ __forceinline__ void odd_even_merge(double (&a)[L]) {
+    if constexpr (2 * R < N) {
+        odd_even_merge<LO, N, 2 * R>(a);
+        odd_even_merge<LO + R, N, 2 * R>(a);
+#pragma unroll
+        for (int i = LO + R; i + R < LO + N; i += 2 * R) order_pair(a[i], a[i + R]);
+    } else {
+        order_pair(a[LO], a[LO + R]);
+    }
+}
+template <int LO, int N, int L>
+__device__ __forceinline__ void sort_descending(double (&a)[L]) {
+    if constexpr (N > 1) {
+        sort_descending<LO, N / 2>(a);
+        sort_descending<LO + N / 2, N / 2>(a);
+        odd_even_merge<LO, N, 1>(a);
+    }
+}
+
+// The set of indices of the first n entries of a sorted list (n per lane).
 template <int L>
-__device__ __forceinline__ void decide_group(const RouteParams& p, const float* row, int tok0, int t, int ntok,
-                                             bool tok_valid, int* cnt) {
-    static_assert(L == 16 || L == 32 || L == 64, "lane groups");
-    const int K = p.K, B = p.B;
-    const int lane = lane_id(), j = lane & (L - 1), gbase = lane - j;
-    const int tok = tok0 + t;
-    const bool in_range = t < ntok;
-    const bool v = in_range && tok_valid;
-    const uint64_t gmask = (L == 64) ? ~0ull : ((1ull << L) - 1ull);
-    auto group_bits = [&](bool pred) { return (ballot(pred) >> gbase) & gmask; };
+__device__ __forceinline__ uint64_t first_indices(const double (&a)[L], int n) {
+    if constexpr (L <= 32) {
+        uint32_t m = 0;   // bit L - 1 - index
+#pragma unroll
+        for (int i = 0; i < L; ++i) m |= (i < n) ? 1u << ((uint32_t)__double2loint(a[i]) & (L - 1)) : 0u;
+        return __brev(m) >> (32 - L);
+    } else {
+        uint64_t m = 0;
+#pragma unroll
+        for (int i = 0; i < L; ++i) m |= (i < n) ? 1ull << ((uint32_t)__double2loint(a[i]) & (L - 1)) : 0ull;
+        return __brevll(m);
+    }
+}
+
+// Orders this wave's LDS accesses for the compiler (a wave's LDS operations
+// execute in order).
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// x / n for x < 2^16 and 1 <= n <= 2^15, with m = div_magic(n).
+__device__ __forceinline__ uint32_t div_magic(int n) { return n > 1 ? 0xffffffffu / (uint32_t)n + 1u : 0u; }
+__device__ __forceinline__ int div_by(int x, uint32_t m) { return m ? (int)__umulhi((uint32_t)x, m) : x; }
+
+// Padded length of the sorted lists: the smallest power of two >= max(K, B),
+// at least 8.
+__host__ __device__ __forceinline__ int decide_length(int K, int B) {
+    const int n = K > B ? K : B;
+    return n <= 8 ? 8 : n <= 16 ? 16 : (n <= 32 ? 32 : 64);
+}
+
+// Decisions of Sec. III-B and III-C for one tile of 64 tokens by one wave,
+// one lane per token. `rows` (LDS, stride p.lstride, odd) holds the tokens'
+// logits: shared demand, K experts, B priorities; `bits` is [B + K + 1]
+// words of LDS. Called by whole waves; tokens past the layer write nothing.
+//   alpha, b    from the shared logit
+//   I_shr       the first b of the sorted priorities
+//   softmax     maximum, exponentials, their sum in index order, fp32
+//   q, p        the sorted affinities
+//   P_r, k      sums p_0..p_r in order; k is the first r whose prefix
+//               reaches the target, else K
+// All arithmetic is the paper's order in fp32 with explicitly rounded
+// operations. With one lane per token nothing crosses lanes until the record
+// is written (through LDS, so the stores are whole lines): 64 tokens cost
+// about as many wave instructions as the 4 tokens of a pass did when a group
+// of lanes shared a token and every broadcast was an LDS permute.
+template <int L>
+__device__ __forceinline__ void decide_tile(const RouteParams& p, float* rows, uint64_t* bits, int tile) {
+    const int K = p.K, B = p.B, ls = p.lstride;
+    const int lane = lane_id(), tok0 = tile * kTileTok, tok = tok0 + lane;
+    const int ntok = min(kTileTok, p.N - tok0);
+    float* row = rows + lane * ls;
+    const bool v = lane < ntok && (p.valid == nullptr || p.valid[tok] != 0);
 
     // Eq. alpha (adaptive) or the fixed-alpha ablation.
     float alpha;
@@ -315,49 +258,45 @@ __device__ __forceinline__ void decide_group(const RouteParams& p, const float* 
     if (p.alpha_mode == 0) b = min(max(b, 1), B - 1);
     b = min(b, p.max_shared);
 
-    // Eq. block-priority / shared-indices: block j is shared when fewer than
-    // b priorities come before it (decreasing, ties to the lower index).
-    bool shared;
+    // Eq. block-priority / shared-indices: the b largest priorities, ties to
+    // the lower index.
+    const uint64_t full = (B == 64) ? ~0ull : ((1ull << B) - 1ull);
+    double a[L];
+    uint64_t mask;
     if (p.select_mode == 0) {
-        const uint32_t uk = j < B ? rank_key(row[1 + K + j]) : 0u;
-        int ru = 0;
-#pragma unroll 16
-        for (int c = 0; c < L; ++c) {
-            const uint32_t o = (uint32_t)__shfl((int)uk, gbase + c);
-            ru += (o > uk) || (o == uk && c < j);
-        }
-        shared = j < B && ru < b;
+#pragma unroll
+        for (int c = 0; c < L; ++c) a[c] = (c < B) ? order_key<L>(row[1 + K + c], c) : 0.0;
+        sort_descending<0, L>(a);
+        mask = first_indices<L>(a, b);
     } else {
-        shared = j < b;
+        mask = (b >= 64) ? ~0ull : ((1ull << b) - 1ull);
     }
-    const uint64_t mask = group_bits(shared);
 
     // Eq. residual-router-score: max-subtracted softmax, index-order sum.
-    const float l = j < K ? row[1 + j] : -INFINITY;
-    float m = l;
+    float e[L];
+    float m = -INFINITY;
 #pragma unroll
-    for (int o = L / 2; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-    const float e = j < K ? expf(__fsub_rn(l, m)) : 0.f;
+    for (int j = 0; j < L; ++j)
+        if (j < K) {
+            e[j] = row[1 + j];
+            m = fmaxf(m, e[j]);
+        }
     float S = 0.f;
-#pragma unroll 16
-    for (int c = 0; c < L; ++c) {
-        const float o = __shfl(e, gbase + c);
-        if (c < K) S = __fadd_rn(S, o);
-    }
-    const float s = __fdiv_rn(e, S);
-    // Eq. sorted-affinity: ranks by decreasing affinity, ties to the lower
-    // index; padding lanes (j >= K) rank after every expert, so the ranks of
-    // the group are a permutation of 0..L-1.
-    const uint32_t sk = j < K ? rank_key(s) : 0u;
-    int rs = 0;
-#pragma unroll 16
-    for (int c = 0; c < L; ++c) {
-        const uint32_t o = (uint32_t)__shfl((int)sk, gbase + c);
-        rs += (o > sk) || (o == sk && c < j);
-    }
-    const int dst = (gbase + rs) << 2;
-    const float ps = __int_as_float(__builtin_amdgcn_ds_permute(dst, __float_as_int(s)));
-    const int qs = __builtin_amdgcn_ds_permute(dst, j + 1);
+#pragma unroll
+    for (int j = 0; j < L; ++j)
+        if (j < K) {
+            e[j] = expf(__fsub_rn(e[j], m));
+            S = __fadd_rn(S, e[j]);
+        }
+    // Eq. sorted-affinity: by decreasing affinity, ties to the lower index.
+#pragma unroll
+    for (int j = 0; j < L; ++j) a[j] = (j < K) ? order_key<L>(__fdiv_rn(e[j], S), j) : 0.0;
+    sort_descending<0, L>(a);
+    // The affinities back as floats (what rank_key maps to them), in order.
+    auto affinity = [&](int i) {
+        const uint32_t r = order_value(a[i]);
+        return __uint_as_float((r & 0x80000000u) ? r & 0x7fffffffu : ~r);
+    };
     // Eq. beta / expert-count: the smallest prefix reaching the target.
     int k;
     if (p.mass_mode == 2) {
@@ -366,26 +305,45 @@ __device__ __forceinline__ void decide_group(const RouteParams& p, const float* 
         const float beta = __fsub_rn(1.0f, alpha);
         const float target = (p.mass_mode == 0) ? fminf(beta, p.t_mass) : p.t_mass;
         float P = 0.f;
-#pragma unroll 16
-        for (int c = 0; c < L; ++c) {
-            const float o = __shfl(ps, gbase + c);
-            if (c <= j && c < K) P = __fadd_rn(P, o);
-        }
-        const uint64_t reached = group_bits(j < K && P >= target);
-        k = reached ? __builtin_ctzll(reached) + 1 : K;
+        bool reached = false;
+        k = 1;
+#pragma unroll
+        for (int i = 0; i < L; ++i)
+            if (i < K) {
+                P = __fadd_rn(P, affinity(i));
+                reached = reached || P >= target;
+                k += reached ? 0 : 1;
+            }
+        k = min(k, K);
     }
+    const uint64_t sel = v ? first_indices<L>(a, k) : 0ull;   // bit j: expert j + 1
 
-    if (in_range) {
-        if (j == 0) {
-            p.alpha[tok] = v ? alpha : 0.f;
-            p.nsh[tok] = v ? b : 0;
-            p.mask[tok] = v ? mask : 0ull;
-            p.nres[tok] = v ? k : 0;
-        }
-        if (j < K) {
-            p.eids[(size_t)tok * K + j] = v ? qs : -1;
-            p.wts[(size_t)tok * K + j] = v ? ps : 0.f;
-        }
+    // The record. Rows of K values per token go through the token's LDS row.
+    if (lane < ntok) {
+        p.alpha[tok] = v ? alpha : 0.f;
+        p.nsh[tok] = v ? b : 0;
+        p.mask[tok] = v ? mask : 0ull;
+        p.nres[tok] = v ? k : 0;
+    }
+    const uint32_t mk = div_magic(K);
+#pragma unroll
+    for (int i = 0; i < L; ++i)
+        if (i < K) row[i] = v ? affinity(i) : 0.f;
+    wave_lds_order();
+    for (int x = lane; x < ntok * K; x += kWave) {
+        const int t = div_by(x, mk);
+        p.wts[(size_t)tok0 * K + x] = rows[t * ls + x - t * K];
+    }
+    wave_lds_order();
+    int* irow = reinterpret_cast<int*>(row);
+    const int* irows = reinterpret_cast<const int*>(rows);
+#pragma unroll
+    for (int i = 0; i < L; ++i)
+        if (i < K) irow[i] = v ? 1 + order_index<L>(a[i]) : -1;
+    wave_lds_order();
+    for (int x = lane; x < ntok * K; x += kWave) {
+        const int t = div_by(x, mk);
+        p.eids[(size_t)tok0 * K + x] = irows[t * ls + x - t * K];
     }
     if (p.bin_count == nullptr) return;
 
@@ -394,119 +352,402 @@ __device__ __forceinline__ void decide_group(const RouteParams& p, const float* 
     // pair adds itself is the pair's slot within that copy (pair_rank), so
     // the scatter needs no atomics; slots inside a bin follow the order the
     // atomics land in, and no result depends on it (every GEMM row is
-    // computed from its own pair).
-    const uint64_t full = (B == 64) ? ~0ull : ((1ull << B) - 1ull);
-    const int kb = p.key_bits;
+    // computed from its own pair). The atomics of a batch are all issued
+    // before a slot is stored.
+    const int kb = p.key_bits, K1 = K + 1;
     const int ks = mask_key(mask, B, kb), kr = mask_key(~mask & full, B, kb);
-    const int bc = (tok / kTileTok) % kBinCopies, nbin = (K + 1) << kb;
-    // Both atomics are issued before either slot is stored (one round trip).
-    int* rank = p.pair_rank + (size_t)(v ? tok : 0) * (K + 1);
-    int r0 = 0, r1 = 0;
-    if (v && j == 0) r0 = atomicAdd(&p.bin_count[bin_counter(ks, bc, nbin)], 1);
-    if (v && j < k) r1 = atomicAdd(&p.bin_count[bin_counter((qs << kb) + kr, bc, nbin)], 1);
-    if (v && j == 0) rank[0] = r0;
-    if (v && j < k) rank[1 + j] = r1;
-    if (cnt == nullptr) return;
-    // The tile's counts: pairs per expert, and rows per slab (the shared
-    // expert on I_shr, each selected residual expert on I_res). Lane c adds
-    // block c's rows.
-    int* ecnt = cnt + (K + 1) * B;
-    if (v && j == 0) atomicAdd(&ecnt[0], 1);
-    if (v && j < k) atomicAdd(&ecnt[qs], 1);
-    if (v && j < B && shared) atomicAdd(&cnt[j], 1);
+    const int bc = tile % kBinCopies, nbin = K1 << kb;
     int kmax = v ? k : 0;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) kmax = max(kmax, __shfl_xor(kmax, o));
-    for (int i = 0; i < kmax; ++i) {
-        const int ei = __shfl(qs, gbase + i);
-        if (v && i < k && j < B && !shared) atomicAdd(&cnt[ei * B + j], 1);
+    kmax = __builtin_amdgcn_readfirstlane(kmax);
+    wave_lds_order();
+    const int kv = v ? k : 0;
+    constexpr int kBatch = 8;
+    int r0 = 0;
+    if (v) r0 = atomicAdd(&p.bin_count[bin_counter(ks, bc, nbin)], 1);
+    for (int i0 = 0; i0 < kmax; i0 += kBatch) {
+        int q[kBatch], s[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) q[u] = (i0 + u < kv) ? irow[i0 + u] : 0;
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+            if (i0 + u < kv) s[u] = atomicAdd(&p.bin_count[bin_counter((q[u] << kb) + kr, bc, nbin)], 1);
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+            if (i0 + u < kv) irow[i0 + u] = s[u];
+    }
+    irow[K] = r0;
+    wave_lds_order();
+    const uint32_t mk1 = div_magic(K1);
+    for (int x = lane; x < ntok * K1; x += kWave) {
+        const int t = div_by(x, mk1), j = x - t * K1;
+        p.pair_rank[(size_t)tok0 * K1 + x] = irows[t * ls + (j == 0 ? K : j - 1)];
+    }
+    if (p.tile_cnt == nullptr) return;
+
+    // The tile's counts (rows per slab: the shared expert on I_shr, each
+    // selected residual expert on I_res; pairs per expert) from the tile's
+    // bit matrices: bits[c] the tokens that share block c, bits[B + e] the
+    // tokens on expert e.
+    uint64_t mine = 0;
+    const uint64_t vm = v ? mask : 0ull;
+    for (int c = 0; c < B; ++c) {
+        const uint64_t t = ballot((vm >> c) & 1ull);
+        mine = (lane == c) ? t : mine;
+    }
+    if (lane < B) bits[lane] = mine;
+    if (lane == 0) bits[B] = 0;
+    const uint64_t all = ballot(v);
+    for (int j = 0; j < K; ++j) {
+        const uint64_t t = ballot((sel >> j) & 1ull);
+        mine = (lane == j) ? t : mine;
+    }
+    if (lane < K) bits[B + 1 + lane] = mine;
+    if (lane == 0) bits[B] = all;
+    wave_lds_order();
+    const int nslab = K1 * B, ncnt = nslab + K1;
+    const uint32_t mb = div_magic(B);
+    int* cnt = p.tile_cnt + (size_t)tile * ncnt;
+    for (int x = lane; x < nslab; x += kWave) {
+        const int ee = div_by(x, mb);
+        const uint64_t sh = bits[x - ee * B], te = bits[B + ee];
+        cnt[x] = __popcll(te & (ee == 0 ? sh : ~sh));
+    }
+    for (int x = lane; x < K1; x += kWave) {
+        const int c = __popcll(bits[B + x]);
+        cnt[nslab + x] = c;
+        // Pairs per expert also into the totals (few atomics, spread).
+        if (c) atomicAdd(&p.exp_total[(tile % kExpCopies) * K1 + x], c);
     }
 }
 
-// Every token of a tile of kTileTok tokens whose logit rows are at `rows`
-// (stride lstride): the waves [w0, w0 + nw) of the workgroup share the
-// tile's tokens, 64 / L per pass.
-template <int L>
-__device__ __forceinline__ void decide_tile(const RouteParams& p, const float* rows, const int* vflags, int tok0,
-                                            int ntok, int wave, int w0, int nw, int* cnt) {
-    constexpr int TPP = 64 / L;   // tokens per wave pass
-    const int g = lane_id() / L;
-    for (int t0 = (wave - w0) * TPP; t0 < kTileTok; t0 += nw * TPP) {
-        const int t = t0 + g;
-        decide_group<L>(p, rows + (size_t)(t < ntok ? t : 0) * p.lstride, tok0, t, ntok, vflags[t] != 0, cnt);
+// decide_tile with the list length of the layer (see decide_length).
+__device__ __forceinline__ void decide_tile_any(const RouteParams& p, float* rows, uint64_t* bits, int tile) {
+    switch (decide_length(p.K, p.B)) {
+        case 8: decide_tile<8>(p, rows, bits, tile); break;
+        case 16: decide_tile<16>(p, rows, bits, tile); break;
+        case 32: decide_tile<32>(p, rows, bits, tile); break;
+        default: decide_tile<64>(p, rows, bits, tile); break;
     }
 }
 
-// The valid flags of a tile's tokens into LDS (1 for every token without a
-// mask; tokens past the layer read 0): the decisions then read them without
-// a global load in each pass. Called by every thread; a barrier follows.
-__device__ __forceinline__ void stage_valid(const RouteParams& p, int tok0, int* vflags) {
-    for (int t = threadIdx.x; t < kTileTok; t += blockDim.x) {
-        const int tok = tok0 + t;
-        vflags[t] = (tok < p.N) ? (p.valid == nullptr ? 1 : (int)p.valid[tok]) : 0;
+// This lane's 8 products of a k step with W_shr added to s in fp32.
+__device__ __forceinline__ float shared_dot(u32x4 x, u32x4 w0, u32x4 w1, float s) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        s = fmaf(__uint_as_float(x[q] << 16), __uint_as_float(q < 2 ? w0[2 * q] : w1[2 * q - 4]), s);
+        s = fmaf(__uint_as_float(x[q] & 0xffff0000u), __uint_as_float(q < 2 ? w0[2 * q + 1] : w1[2 * q - 3]), s);
     }
+    return s;
 }
 
-// The workgroup's tile counters (ncnt words per tile, in LDS) out to memory
-// once its tiles are decided: tile i of the workgroup is layer tile
-// tile0 + i * stride. Called by every thread after a barrier.
-__device__ __forceinline__ void flush_counts(const RouteParams& p, const int* cnt, int ntiles, int ncnt, int tile0,
-                                             int stride) {
-    const int nslab = (p.K + 1) * p.B;
-    for (int x = threadIdx.x; x < ncnt; x += blockDim.x)
-        for (int i = 0; i < ntiles; ++i) {
-            const int tile = tile0 + i * stride, c = cnt[i * ncnt + x];
-            p.tile_cnt[(size_t)tile * ncnt + x] = c;
-            // Pairs per expert also into the totals (few atomics, spread).
-            if (x >= nslab && c) atomicAdd(&p.exp_total[(tile % kExpCopies) * (p.K + 1) + x - nslab], c);
-        }
-}
-
-// The decisions of one tile with the lane count of the layer (see
-// decide_lanes).
-__device__ __forceinline__ void decide_tile_any(const RouteParams& p, const float* rows, const int* vflags, int tok0,
-                                                int ntok, int wave, int w0, int nw, int* cnt) {
-    switch (decide_lanes(p.K, p.B)) {
-        case 16: decide_tile<16>(p, rows, vflags, tok0, ntok, wave, w0, nw, cnt); break;
-        case 32: decide_tile<32>(p, rows, vflags, tok0, ntok, wave, w0, nw, cnt); break;
-        default: decide_tile<64>(p, rows, vflags, tok0, ntok, wave, w0, nw, cnt); break;
-    }
-}
-
-// NCT: 16-column logit tiles of the bf16 path (1 + K + B <= 16 NCT); 0 for
-// fp32 tokens. One workgroup of 4 waves per kRouteTok tokens (two tiles):
-// the logits of all of them, then the two tiles' decisions, all 4 waves on
-// each tile. The last p.cvt_blocks workgroups do the launch's copy job.
+// One wave's (partial) logits of its 64 tokens into LDS rows of stride ls:
+// column 0 the shared demand, columns 1.. the MFMA tiles.
 template <int NCT>
-__global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteParams p) {
-    constexpr int NT = kRouteTok / kTileTok;
+__device__ __forceinline__ void put_logits(float* P, int ls, const f32x4 (&acc)[4][NCT], const float (&sh)[4]) {
+    const int lane = lane_id();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        float v = sh[r];
+        v += __shfl_xor(v, 16);
+        v += __shfl_xor(v, 32);
+        if (lane < 16) P[(r * 16 + lane) * ls] = v;
+#pragma unroll
+        for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                P[(r * 16 + (lane >> 4) * 4 + e) * ls + 1 + ct * 16 + (lane & 15)] = acc[r][ct][e];
+    }
+}
+
+// One tile per workgroup of kSplitWaves waves, which share the contraction;
+// the partial logits are summed in wave order and wave 0 decides the tile.
+// For few tiles the chain of k steps of one wave sets the time, and this
+// splits it: up to 256 tiles (one per compute unit) it is as fast as either
+// other form or faster (16,384 tokens of d = 768, K = B = 16: 21 us against
+// 25 us in two launches; d = 1024, K = B = 32: 38 against 46 us), past that
+// the router rows it re-reads per tile make it slower (32,768: 39 against 32
+// us, 71 against 47 us). NCT: 16-column tiles of the bf16 router; 0: fp32 tokens. The
+// last p.cvt_blocks workgroups do the launch's copy job.
+constexpr int kSplitWaves = 4;
+
+template <int NCT>
+__device__ __forceinline__ void split_k_logits_bf16(const RouteParams& p, float* P, int tok0, int wave) {
+    constexpr int RT = kTileTok / 16;
+    const int lane = lane_id();
+    const u16* X = static_cast<const u16*>(p.X);
+    f32x4 acc[RT][NCT];
+    float sh[RT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+        sh[i] = 0.f;
+#pragma unroll
+        for (int j = 0; j < NCT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const int kof = (lane >> 4) * 8;
+    const u16* xr[RT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)   // rows past N read row N - 1; their logits are never used
+        xr[i] = X + (size_t)min(tok0 + i * 16 + (lane & 15), p.N - 1) * p.d + kof;
+    const float* wsh = p.Wr + kof;           // row 0 of the fp32 router: W_shr
+    const int nks = p.d / 32;
+    const int ks0 = wave * nks / kSplitWaves, n = (wave + 1) * nks / kSplitWaves - ks0;
+    // Every operand of a k step is loaded together, a step ahead of its use.
+    struct Set {
+        u32x4 a[RT], b[3][NCT], s0, s1;
+    };
+    Set ring[2];
+    auto load = [&](int ks, Set& S) {
+        const int k0 = (ks0 + ks) * 32;
+#pragma unroll
+        for (int i = 0; i < RT; ++i) S.a[i] = ld16(xr[i] + k0);
+#pragma unroll
+        for (int part = 0; part < 3; ++part)
+#pragma unroll
+            for (int ct = 0; ct < NCT; ++ct)
+                S.b[part][ct] = ld16(p.Wsplit + split_at(16 * NCT, part, ct * 16 + (lane & 15), k0 + kof));
+        S.s0 = ld16(wsh + k0);
+        S.s1 = ld16(wsh + k0 + 4);
+    };
+    auto compute = [&](const Set& S) {
+#pragma unroll
+        for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+            for (int part = 0; part < 3; ++part) {
+                const bf16x8 b = as_bf16x8(S.b[part][ct]);
+#pragma unroll
+                for (int i = 0; i < RT; ++i) acc[i][ct] = mfma16x16x32(as_bf16x8(S.a[i]), b, acc[i][ct]);
+            }
+#pragma unroll
+        for (int i = 0; i < RT; ++i) sh[i] = shared_dot(S.a[i], S.s0, S.s1, sh[i]);
+    };
+    if (n > 0) load(0, ring[0]);
+    for (int ks = 0; ks < n; ks += 2) {
+        if (ks + 1 < n) load(ks + 1, ring[1]);
+        compute(ring[0]);
+        if (ks + 1 < n) {
+            if (ks + 2 < n) load(ks + 2, ring[0]);
+            compute(ring[1]);
+        }
+    }
+    put_logits<NCT>(P, p.lstride, acc, sh);
+}
+
+// fp32 tokens: all 1 + K + B columns on the matrix cores in fp32, 64 columns
+// at a time. Lane l brings row l % 16 of its operand and, per 16 k, the four
+// values k0 + 4 (l / 16) + 0..3, one per product (both operands take the same
+// k, in whatever order). d need not be a multiple of 16 nor the rows aligned.
+__device__ __forceinline__ void split_k_logits_f32(const RouteParams& p, float* P, int tok0, int wave) {
+    constexpr int RT = kTileTok / 16, CT = 4;
+    const int lane = lane_id(), kof = (lane >> 4) * 4;
+    const float* X = static_cast<const float*>(p.X);
+    const int nks = ceil_div(p.d, 16);
+    const int ks0 = wave * nks / kSplitWaves, ks1 = (wave + 1) * nks / kSplitWaves;
+    auto load4 = [&](const float* r, int k) {   // r[k..k+3], zero past d
+        f32x4 v;
+        if (k + 4 <= p.d) {
+            v = ld_f32x4(r + k);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = (k + i < p.d) ? r[k + i] : 0.f;
+        }
+        return v;
+    };
+    const float* xr[RT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i) xr[i] = X + (size_t)min(tok0 + i * 16 + (lane & 15), p.N - 1) * p.d;
+    for (int c0 = 0; c0 < p.NL; c0 += 16 * CT) {
+        const float* wr[CT];
+#pragma unroll
+        for (int j = 0; j < CT; ++j) {
+            const int c = min(c0 + j * 16 + (lane & 15), p.NL - 1);
+            wr[j] = (c <= p.K) ? p.Wr + (size_t)c * p.d : p.mu + (size_t)(c - 1 - p.K) * p.d;
+        }
+        f32x4 acc[RT][CT];
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int j = 0; j < CT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int ks = ks0; ks < ks1; ++ks) {
+            f32x4 x[RT], w[CT];
+#pragma unroll
+            for (int i = 0; i < RT; ++i) x[i] = load4(xr[i], ks * 16 + kof);
+#pragma unroll
+            for (int j = 0; j < CT; ++j) w[j] = load4(wr[j], ks * 16 + kof);
+#pragma unroll
+            for (int j = 0; j < CT; ++j)
+                if (c0 + j * 16 < p.NL)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int i = 0; i < RT; ++i)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i][q], w[j][q], acc[i][j], 0, 0, 0);
+        }
+#pragma unroll
+        for (int j = 0; j < CT; ++j) {
+            const int c = c0 + j * 16 + (lane & 15);
+            if (c < p.NL)
+#pragma unroll
+                for (int i = 0; i < RT; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) P[(i * 16 + (lane >> 4) * 4 + e) * p.lstride + c] = acc[i][j][e];
+        }
+    }
+}
+
+template <int NCT>
+__global__ __launch_bounds__(kSplitWaves * 64) void route_split_k_kernel(RouteParams p) {
     if (route_copy_role(p)) return;
-    extern __shared__ float lds_route[];
-    float* L = lds_route;
-    const int ncnt = (p.K + 1) * p.B + p.K + 1;
-    int* cnt = reinterpret_cast<int*>(L + kRouteTok * p.lstride);   // [NT][ncnt]
-    int* vflags = cnt + NT * ncnt;                                   // [NT][kTileTok]
-    const int tok0 = blockIdx.x * kRouteTok;
-    const bool counting = p.tile_cnt != nullptr;
-    if (counting)
-        for (int i = threadIdx.x; i < NT * ncnt; i += blockDim.x) cnt[i] = 0;
-    for (int h = 0; h < NT; ++h) stage_valid(p, tok0 + h * kTileTok, vflags + h * kTileTok);
-    if constexpr (NCT > 0) route_logits_bf16<NCT>(p, L, tok0);
-    else route_logits_f32(p, L, tok0);
+    extern __shared__ __attribute__((aligned(16))) float lds_route[];
+    const int ls = p.lstride, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int tile = blockIdx.x, part = kTileTok * ls;
+    if constexpr (NCT > 0) split_k_logits_bf16<NCT>(p, lds_route + wave * part, tile * kTileTok, wave);
+    else split_k_logits_f32(p, lds_route + wave * part, tile * kTileTok, wave);
     __syncthreads();
-    const int wave = threadIdx.x >> 6;
-    int nt = 0;
-    for (int h = 0; h < NT; ++h) {
-        const int t0 = tok0 + h * kTileTok;
-        if (t0 >= p.N) break;
-        decide_tile_any(p, L + (size_t)h * kTileTok * p.lstride, vflags + h * kTileTok, t0, min(kTileTok, p.N - t0),
-                        wave, 0, kRouteThreads / 64, counting ? cnt + h * ncnt : nullptr);
-        ++nt;
+    for (int x = threadIdx.x; x < part; x += kSplitWaves * 64) {
+        float v = 0.f;
+#pragma unroll
+        for (int w = 0; w < kSplitWaves; ++w) v += lds_route[w * part + x];
+        lds_route[x] = v;
     }
-    if (counting) {
+    __syncthreads();
+    if (wave == 0) decide_tile_any(p, lds_route, reinterpret_cast<uint64_t*>(lds_route + kSplitWaves * part), tile);
+}
+
+// bf16 routers of any width over many tokens: 4 waves, one 64-token tile
+// each. The router's three parts stream through LDS 64 k at a time (one
+// 128-byte line per row, the GEMM engine's swizzle; two slots), shared by the
+// four tiles, the token rows into registers, both one stage ahead; then each
+// wave decides its own tile from its logits in LDS (no logits in memory).
+// What bounds it is the HBM read of X and, per stage, the chain of fragment
+// reads and products of one wave (two workgroups share a compute unit, so
+// registers are the limit: W_shr goes through LDS and only one step's
+// fragments are read ahead; with spills in the loop a stage took 4 us, since
+// every reload waits behind the copies in flight). d = 1024, K = B = 32:
+// 100,001 tokens 477 us with one fused kernel of 4 tokens per decision pass,
+// 79 us here; 32,768 tokens 71 us with a tile per workgroup, 47 us here.
+// The last p.cvt_blocks workgroups do the launch's copy job.
+constexpr int kWideWaves = 4;
+
+template <int NCT>
+__global__ __launch_bounds__(kWideWaves * 64, NCT <= 4 ? 2 : 1) void route_wide_kernel(RouteParams p) {
+    if (route_copy_role(p)) return;
+    constexpr int RT = kTileTok / 16, ROWS = 48 * NCT, COPIES = ROWS / 8, SLOT = ROWS * 128;
+    extern __shared__ __attribute__((aligned(16))) float lds_route[];
+    char* const stage = reinterpret_cast<char*>(lds_route);
+    char* const shr = stage + 2 * SLOT;
+    const int ls = p.lstride, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int tile = blockIdx.x * kWideWaves + wave, tok0 = tile * kTileTok;
+    const u16* X = static_cast<const u16*>(p.X);
+    const int nks = p.d / 32, nst = (nks + 1) / 2;
+    const int kof = (lane >> 4) * 8;
+    const u16* xr[RT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)   // rows past N read row N - 1; their logits are never used
+        xr[i] = X + (size_t)min(tok0 + i * 16 + (lane & 15), p.N - 1) * p.d + kof;
+    f32x4 acc[RT][NCT];
+    float sh[RT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+        sh[i] = 0.f;
+#pragma unroll
+        for (int j = 0; j < NCT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    auto copy_stage = [&](int st) {
+        char* base = stage + (st & 1) * SLOT;
+        for (int q = wave; q < COPIES; q += kWideWaves) {
+            const int r = q * 8 + (lane >> 3);
+            dma16(p.Wsplit + ((size_t)st * ROWS + r) * 64 + 8 * ((lane & 7) ^ ((r >> 1) & 7)), base + q * 1024);
+        }
+        if (wave == 0) dma4(p.Wr + min(st * 64 + lane, p.d - 1), shr + (st & 1) * 256);   // W_shr
+    };
+    struct Set {
+        u32x4 a[2][RT];
+    };
+    Set ring[2];
+    auto load = [&](int st, Set& S) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int k0 = min(2 * st + h, nks - 1) * 32;
+#pragma unroll
+            for (int i = 0; i < RT; ++i) S.a[h][i] = ld16(xr[i] + k0);
+        }
+    };
+    // The router's fragments of step x of a stage: column tile x / 2, k step
+    // x % 2, three parts.
+    auto fragments = [&](int st, int x, u32x4 (&w)[3]) {
+        const char* base = stage + (st & 1) * SLOT;
+#pragma unroll
+        for (int part = 0; part < 3; ++part) {
+            const int r = part * 16 * NCT + (x >> 1) * 16 + (lane & 15);
+            w[part] = ld16(base + r * 128 + (((4 * (x & 1) + (lane >> 4)) ^ ((r >> 1) & 7)) << 4));
+        }
+    };
+    // A stage's products are summed on their own, small parts first, and then
+    // added to the logits: a sixth of the roundings at the logits' magnitude
+    // that one running accumulator would take. The next step's fragments are
+    // read while this one's are multiplied.
+    auto compute = [&](int st, const Set& S) {
+        const bool both = 2 * st + 1 < nks;   // the last stage of an odd count of k steps has one
+        u32x4 w[2][3];
+        f32x4 t[RT];
+        fragments(st, 0, w[0]);
+#pragma unroll
+        for (int x = 0; x < 2 * NCT; ++x) {
+            if (x + 1 < 2 * NCT) fragments(st, x + 1, w[(x + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+            if ((x & 1) == 0) {
+#pragma unroll
+                for (int i = 0; i < RT; ++i) t[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+            if ((x & 1) == 0 || both) {
+#pragma unroll
+                for (int part = 2; part >= 0; --part)
+#pragma unroll
+                    for (int i = 0; i < RT; ++i)
+                        t[i] = mfma16x16x32(as_bf16x8(S.a[x & 1][i]), as_bf16x8(w[x & 1][part]), t[i]);
+            }
+            if (x & 1) {
+#pragma unroll
+                for (int i = 0; i < RT; ++i) acc[i][x >> 1] += t[i];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const char* ws = shr + (st & 1) * 256 + kof * 4;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if (h == 1 && !both) break;
+            const u32x4 s0 = ld16(ws + h * 128), s1 = ld16(ws + h * 128 + 16);
+#pragma unroll
+            for (int i = 0; i < RT; ++i) sh[i] = shared_dot(S.a[h][i], s0, s1, sh[i]);
+        }
+    };
+    // At the top of a stage its copies and rows have landed and every wave
+    // has left the slot that the next stage fills.
+    auto step = [&](int st, const Set& S, Set& next) {
+        wait_vmcnt<0>();
         __syncthreads();
-        flush_counts(p, cnt, nt, ncnt, tok0 / kTileTok, 1);
+        if (st + 1 < nst) {
+            copy_stage(st + 1);
+            load(st + 1, next);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        compute(st, S);
+    };
+    copy_stage(0);
+    load(0, ring[0]);
+    for (int st = 0; st < nst; st += 2) {
+        step(st, ring[0], ring[1]);
+        if (st + 1 < nst) step(st + 1, ring[1], ring[0]);
     }
+    __syncthreads();   // the logit rows take the place of the stages
+    float* rows = lds_route + wave * kTileTok * ls;
+    put_logits<NCT>(rows, ls, acc, sh);
+    wave_lds_order();
+    if (tok0 >= p.N) return;
+    uint64_t* bits = reinterpret_cast<uint64_t*>(lds_route + kWideWaves * kTileTok * ls) + wave * (p.B + p.K + 1);
+    decide_tile_any(p, rows, bits, tile);
 }
 
 // Logits of bf16 tokens when the router fits in registers (1 + K + B <= 32
@@ -538,8 +779,6 @@ __global__ __launch_bounds__(kRpThreads) void route_logits_kernel(RouteParams p,
     const int nks = p.d / 32;
     const int kb = wave * nks / kRpWaves, kn = (wave + 1) * nks / kRpWaves - kb;   // kn <= KPW
     const int kof = (lane >> 4) * 8;
-    const u16* wb = p.Wsplit + (size_t)(lane & 15) * p.d + kof;
-    const size_t part_stride = (size_t)p.NLP * p.d, ct_stride = (size_t)16 * p.d;
     u32x4 W[KPW][3][NCT], S0[KPW], S1[KPW];
 #pragma unroll
     for (int j = 0; j < KPW; ++j) {
@@ -547,7 +786,8 @@ __global__ __launch_bounds__(kRpThreads) void route_logits_kernel(RouteParams p,
 #pragma unroll
         for (int part = 0; part < 3; ++part)
 #pragma unroll
-            for (int ct = 0; ct < NCT; ++ct) W[j][part][ct] = ld16(wb + part * part_stride + ct * ct_stride + k0);
+            for (int ct = 0; ct < NCT; ++ct)
+                W[j][part][ct] = ld16(p.Wsplit + split_at(16 * NCT, part, ct * 16 + (lane & 15), k0 + kof));
         S0[j] = ld16(p.Wr + kof + k0);
         S1[j] = ld16(p.Wr + kof + k0 + 4);
     }
@@ -585,34 +825,14 @@ __global__ __launch_bounds__(kRpThreads) void route_logits_kernel(RouteParams p,
                         for (int r = 0; r < RT; ++r)
                             acc[r][ct] = mfma16x16x32(as_bf16x8(xa[j][r]), as_bf16x8(W[j][part][ct]), acc[r][ct]);
 #pragma unroll
-                for (int r = 0; r < RT; ++r)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const uint32_t u = xa[j][r][q];
-                        sh[r] = fmaf(__uint_as_float(u << 16), __uint_as_float(q < 2 ? S0[j][2 * q] : S1[j][2 * q - 4]), sh[r]);
-                        sh[r] = fmaf(__uint_as_float(u & 0xffff0000u),
-                                     __uint_as_float(q < 2 ? S0[j][2 * q + 1] : S1[j][2 * q - 3]), sh[r]);
-                    }
+                for (int r = 0; r < RT; ++r) sh[r] = shared_dot(xa[j][r], S0[j], S1[j], sh[r]);
             }
         }
         // The next tile's rows are in flight during the reduction.
         if (i + 1 < nt) load_x(i + 1);
-        // This wave's partial logits: column 0 the shared demand, columns
-        // 1.. the MFMA tiles. (The barrier after the previous tile's sum
-        // orders its reads of Pbuf before these writes.)
-        float* P = Pbuf + wave * kRpTok * ls;
-#pragma unroll
-        for (int r = 0; r < RT; ++r) {
-            float v = sh[r];
-            v += __shfl_xor(v, 16);
-            v += __shfl_xor(v, 32);
-            if (lane < 16) P[(r * 16 + lane) * ls] = v;
-#pragma unroll
-            for (int ct = 0; ct < NCT; ++ct)
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    P[(r * 16 + (lane >> 4) * 4 + e) * ls + 1 + ct * 16 + (lane & 15)] = acc[r][ct][e];
-        }
+        // This wave's partial logits. (The barrier after the previous tile's
+        // sum orders its reads of Pbuf before these writes.)
+        put_logits<NCT>(Pbuf + wave * kRpTok * ls, ls, acc, sh);
         lds_barrier();
         // Sum of the 8 k slices, in wave order, straight to memory.
         const int ntok = min(kRpTok, p.N - tok0);
@@ -627,46 +847,19 @@ __global__ __launch_bounds__(kRpThreads) void route_logits_kernel(RouteParams p,
     }
 }
 
-// Decisions of one 64-token tile per workgroup of NW waves (L lanes per
-// token, see decide_lanes), from the logits route_logits_kernel wrote (ncols
-// per token), staged in LDS rows; then the tile's counters out to memory.
-// The last p.cvt_blocks workgroups do the launch's copy job instead. With
-// few tiles (up to two per compute unit) 8 waves share a tile, so each wave
-// runs half the passes of dependent lane exchanges; with more tiles 4 do,
-// which leaves room on each compute unit for more tiles and the copy.
-template <int L, int NW>
-__global__ __launch_bounds__(NW * 64) void route_decide_kernel(RouteParams p, const float* __restrict__ logits,
-                                                               int ncols) {
+// Decisions from the logits route_logits_kernel wrote ([N][lstride]), one
+// 64-token tile per one-wave workgroup. The last p.cvt_blocks workgroups do
+// the launch's copy job instead.
+template <int L>
+__global__ __launch_bounds__(64) void route_decide_kernel(RouteParams p, const float* __restrict__ logits) {
     if (route_copy_role(p)) return;
-    extern __shared__ float lds_dec[];
-    const int ls = p.lstride;
-    float* rows = lds_dec;                                       // [64][ls]
-    const int ncnt = (p.K + 1) * p.B + p.K + 1;
-    int* cnt = reinterpret_cast<int*>(rows + kTileTok * ls);     // the tile's counters
-    int* vflags = cnt + ncnt;                                    // [kTileTok] valid flags
-    const bool counting = p.tile_cnt != nullptr;
+    extern __shared__ __attribute__((aligned(16))) float lds_dec[];
     const int tile = blockIdx.x, tok0 = tile * kTileTok, ntok = min(kTileTok, p.N - tok0);
-    // The tokens' valid flags are loaded first and stored after the logit
-    // rows' batch, so their latencies overlap.
-    const int tv = (int)threadIdx.x;
-    uint32_t vb = 1u;
-    if (tv < ntok && p.valid != nullptr) vb = p.valid[tok0 + tv];
-    batched_copy(
-        ntok * ncols, [&](int e) { return logits[(size_t)tok0 * ncols + e]; },
-        [&](int e, float v) {
-            const int t = e / ncols;
-            rows[t * ls + e - t * ncols] = v;
-        });
-    asm volatile("" : "+v"(vb));   // the byte is first used here, after the rows' batch
-    if (tv < kTileTok) vflags[tv] = (tv < ntok && vb != 0u) ? 1 : 0;
-    if (counting)
-        for (int i = threadIdx.x; i < ncnt; i += blockDim.x) cnt[i] = 0;
-    __syncthreads();
-    decide_tile<L>(p, rows, vflags, tok0, ntok, (int)threadIdx.x >> 6, 0, NW, counting ? cnt : nullptr);
-    if (counting) {
-        __syncthreads();
-        flush_counts(p, cnt, 1, ncnt, tile, 1);
-    }
+    const float* src = logits + (size_t)tok0 * p.lstride;
+    // Rows past the layer keep whatever LDS holds; they are not decided.
+    batched_copy(ntok * p.lstride, [&](int i) { return src[i]; }, [&](int i, float v) { lds_dec[i] = v; });
+    wave_lds_order();
+    decide_tile<L>(p, lds_dec, reinterpret_cast<uint64_t*>(lds_dec + kTileTok * p.lstride), tile);
 }
 
 }  // namespace unifmoe

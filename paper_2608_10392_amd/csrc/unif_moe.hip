@@ -52,6 +52,9 @@ namespace {
 constexpr int kKeyBitsMax = 10;
 constexpr int kPhaseEvents = 7;   // unif_moe_layer_forward_profiled
 constexpr size_t kLdsLimit = 160 * 1024;
+// Up to this many 64-token tiles the routing runs in one launch of one tile
+// per workgroup (route_split_k_kernel).
+constexpr int kSplitKTiles = 256;
 
 // Expert-GEMM tile shapes, one workgroup of 8 waves per CU. Up: 256 or 384
 // gathered rows x the whole block width M. Down: see down_shape.
@@ -124,17 +127,17 @@ unif_moe_config worst_case(unif_moe_config c) {
 
 // Counters per tile of the permutation: rows per slab, then pairs per expert.
 size_t tile_counters(const Dims& m) { return (size_t)m.nslab + m.K1; }
-// Routing LDS (route_kernel): the logit rows of its tokens, then its two
-// tiles' counters and their tokens' valid flags.
-size_t route_lds_bytes(const Dims& m) {
-    return sizeof(float) * ((size_t)kRouteTok * m.lstride + (kRouteTok / kTileTok) * (tile_counters(m) + kTileTok));
+// Routing LDS: logit rows of 64 tokens per wave (the wide kernel's share the
+// space with its stages of router rows), then the bit matrices of the tiles a
+// workgroup decides.
+size_t tile_logits_bytes(const Dims& m) { return sizeof(float) * kTileTok * (size_t)m.lstride; }
+size_t tile_bits_bytes(const Dims& m) { return sizeof(uint64_t) * (size_t)(m.B + m.K1); }
+size_t route_split_k_lds_bytes(const Dims& m) { return kSplitWaves * tile_logits_bytes(m) + tile_bits_bytes(m); }
+size_t route_wide_lds_bytes(const Dims& m) {
+    return std::max((size_t)2 * (3 * m.NLP * 128 + 256), kWideWaves * (tile_logits_bytes(m) + tile_bits_bytes(m)));
 }
-// The persistent logits kernel: 8 partial logit sets of a tile. The
-// decisions kernel: a tile's logit rows, counters and valid flags.
-size_t route_logits_lds_bytes(const Dims& m) { return sizeof(float) * (size_t)kRpWaves * kRpTok * m.lstride; }
-size_t route_decide_lds_bytes(const Dims& m) {
-    return sizeof(float) * ((size_t)kTileTok * m.lstride + tile_counters(m) + kTileTok);
-}
+size_t route_logits_lds_bytes(const Dims& m) { return kRpWaves * tile_logits_bytes(m); }
+size_t route_decide_lds_bytes(const Dims& m) { return tile_logits_bytes(m) + tile_bits_bytes(m); }
 // Logits of the split routing path (bf16 routers of <= 32 columns, d <= 1024):
 // 1 + 16 NCT fp32 values per token, or 0 when the path does not apply.
 int split_route_cols(const Dims& m) {
@@ -171,9 +174,7 @@ int32_t check_config(const unif_moe_config* c) {
     if (c->n_blocks > 64 || c->n_experts > 64) return UNIF_EUNSUPPORTED;
     const int64_t N = c->n_tokens, K = c->n_experts, B = c->n_blocks;
     if (N * (K + 1) > INT32_MAX || N * K * B > INT32_MAX) return UNIF_EUNSUPPORTED;
-    const Dims m = dims_of(c);
-    if (route_lds_bytes(m) > kLdsLimit) return UNIF_EUNSUPPORTED;
-    if (m.bf16 && (m.d % 32) != 0) return UNIF_EUNSUPPORTED;
+    if (c->dtype == UNIF_BF16 && c->d_model % 32 != 0) return UNIF_EUNSUPPORTED;
     return UNIF_OK;
 }
 
@@ -235,7 +236,7 @@ struct RoutePlan {
 RoutePlan plan_route(const Dims& m) {
     Carver cv;
     RoutePlan p;
-    p.wsplit = cv.take(m.bf16 ? (size_t)3 * m.NLP * m.d * sizeof(u16) : 0);
+    p.wsplit = cv.take(m.bf16 ? split_at(m.NLP, 0, 0, ceil_div(m.d, 64) * 64) * sizeof(u16) : 0);
     p.logits = cv.take((size_t)m.N * split_route_cols(m) * sizeof(float));
     p.total = cv.cur;
     return p;
@@ -285,7 +286,7 @@ FwdPlan plan_forward(const Dims& m, size_t xn_bytes = 0) {
     p.nres = cv.take(4 * N);
     p.eids = cv.take(4 * N * K);
     p.wts = cv.take(4 * N * K);
-    p.wsplit = cv.take(m.bf16 ? (size_t)3 * m.NLP * m.d * sizeof(u16) : 0);
+    p.wsplit = cv.take(m.bf16 ? split_at(m.NLP, 0, 0, ceil_div(m.d, 64) * 64) * sizeof(u16) : 0);
     p.logits = cv.take((size_t)N * split_route_cols(m) * sizeof(float));
     p.bin_count = cv.take(4 * (size_t)m.nbin * kBinCopies);
     p.zero_begin = p.bin_count;
@@ -407,7 +408,7 @@ RouteParams route_params(const unif_moe_config* c, const Dims& m, const void* X,
 // Router logits and decisions (shared by unif_moe_route and the forward).
 // The forward's counters (zwords words at zero) are cleared in the launch
 // that splits the router weights.
-int32_t launch_route(const Dims& m, const RouteParams& rp, const float* Wr, const float* mu, u16* wsplit,
+int32_t launch_route(const Dims& m, RouteParams rp, const float* Wr, const float* mu, u16* wsplit,
                      float* logits, hipStream_t st, uint32_t* zero = nullptr, size_t zwords = 0) {
     if (m.N == 0) return UNIF_OK;
     const int nsplit = m.bf16 ? ceil_div(m.NLP * m.d, 256) : 0;
@@ -417,11 +418,16 @@ int32_t launch_route(const Dims& m, const RouteParams& rp, const float* Wr, cons
                                                            zwords);
         UNIF_LAUNCH_CHECK();
     }
-    // Small bf16 routers: logits (router in registers), then decisions.
-    const int ncols = split_route_cols(m);
-    if (ncols > 0 && logits != nullptr) {
+    const int ntiles = ceil_div(m.N, kTileTok), nct = m.NLP / 16, cus = cu_count();
+    // The copy job's share of a launch: at most 8 waves per compute unit.
+    auto copy_blocks = [&](int threads) {
+        return (int)std::min<size_t>(ceil_div_sz(rp.cvt_n8, threads), (size_t)cus * (512 / threads));
+    };
+    // bf16 routers of at most 32 columns: logits (router in registers), then
+    // decisions.
+    if (split_route_cols(m) > 0 && logits != nullptr && ntiles > kSplitKTiles) {
         void (*lk)(RouteParams, float*) = nullptr;
-        const int nct = m.NLP / 16, kpw = ceil_div(m.d / 32, kRpWaves);
+        const int kpw = ceil_div(m.d / 32, kRpWaves);
         switch (nct * 4 + kpw) {
             case 5: lk = route_logits_kernel<1, 1>; break;
             case 6: lk = route_logits_kernel<1, 2>; break;
@@ -433,40 +439,42 @@ int32_t launch_route(const Dims& m, const RouteParams& rp, const float* Wr, cons
             case 12: lk = route_logits_kernel<2, 4>; break;
             default: return UNIF_EUNSUPPORTED;
         }
-        void (*dk)(RouteParams, const float*, int) = nullptr;
-        const int ntiles = ceil_div(m.N, kRpTok);
-        const bool wide = ntiles <= 2 * cu_count();   // 8 waves per tile
-        switch (decide_lanes(m.K, m.B)) {
-            case 16: dk = wide ? route_decide_kernel<16, 8> : route_decide_kernel<16, 4>; break;
-            case 32: dk = wide ? route_decide_kernel<32, 8> : route_decide_kernel<32, 4>; break;
-            default: dk = wide ? route_decide_kernel<64, 8> : route_decide_kernel<64, 4>; break;
+        void (*dk)(RouteParams, const float*) = nullptr;
+        switch (decide_length(m.K, m.B)) {
+            case 8: dk = route_decide_kernel<8>; break;
+            case 16: dk = route_decide_kernel<16>; break;
+            default: dk = route_decide_kernel<32>; break;   // K + B <= 32
         }
         const size_t l1 = route_logits_lds_bytes(m), l2 = route_decide_lds_bytes(m);
         if (allow_lds(lk, l1) != UNIF_OK || allow_lds(dk, l2) != UNIF_OK) return UNIF_EDEVICE;
-        lk<<<std::min(cu_count(), ntiles), kRpThreads, l1, st>>>(rp, logits);
+        rp.cvt_blocks = copy_blocks(64);
+        lk<<<std::min(cus, ntiles), kRpThreads, l1, st>>>(rp, logits);
         UNIF_LAUNCH_CHECK();
-        dk<<<ntiles + rp.cvt_blocks, wide ? 512 : 256, l2, st>>>(rp, logits, ncols);
+        dk<<<ntiles + rp.cvt_blocks, 64, l2, st>>>(rp, logits);
         UNIF_LAUNCH_CHECK();
         return UNIF_OK;
     }
-    const size_t lds = route_lds_bytes(m);
-    const int grid = ceil_div(m.N, kRouteTok);
-    void (*kern)(RouteParams) = route_kernel<0>;
+    // Logits and decisions in one launch.
+    const bool wide = m.bf16 && ntiles > kSplitKTiles;
+    void (*kern)(RouteParams) = route_split_k_kernel<0>;
     if (m.bf16) {
-        switch (m.NLP / 16) {
-            case 1: kern = route_kernel<1>; break;
-            case 2: kern = route_kernel<2>; break;
-            case 3: kern = route_kernel<3>; break;
-            case 4: kern = route_kernel<4>; break;
-            case 5: kern = route_kernel<5>; break;
-            case 6: kern = route_kernel<6>; break;
-            case 7: kern = route_kernel<7>; break;
-            case 8: kern = route_kernel<8>; break;
+        switch (nct) {
+            case 1: kern = wide ? route_wide_kernel<1> : route_split_k_kernel<1>; break;
+            case 2: kern = wide ? route_wide_kernel<2> : route_split_k_kernel<2>; break;
+            case 3: kern = wide ? route_wide_kernel<3> : route_split_k_kernel<3>; break;
+            case 4: kern = wide ? route_wide_kernel<4> : route_split_k_kernel<4>; break;
+            case 5: kern = wide ? route_wide_kernel<5> : route_split_k_kernel<5>; break;
+            case 6: kern = wide ? route_wide_kernel<6> : route_split_k_kernel<6>; break;
+            case 7: kern = wide ? route_wide_kernel<7> : route_split_k_kernel<7>; break;
+            case 8: kern = wide ? route_wide_kernel<8> : route_split_k_kernel<8>; break;
             default: return UNIF_EUNSUPPORTED;
         }
     }
+    const size_t lds = wide ? route_wide_lds_bytes(m) : route_split_k_lds_bytes(m);
+    const int grid = wide ? ceil_div(ntiles, kWideWaves) : ntiles;
     if (allow_lds(kern, lds) != UNIF_OK) return UNIF_EDEVICE;
-    kern<<<grid + rp.cvt_blocks, kRouteThreads, lds, st>>>(rp);
+    rp.cvt_blocks = copy_blocks(256);
+    kern<<<grid + rp.cvt_blocks, 256, lds, st>>>(rp);
     UNIF_LAUNCH_CHECK();
     return UNIF_OK;
 }
@@ -645,7 +653,6 @@ int32_t forward_impl(const unif_moe_config* cfg, const unif_moe_block* blk, cons
         rp.cvt_src = static_cast<const u16*>(W_down);
         rp.cvt_dst = reinterpret_cast<u16*>(ws + plan.wdown16);
         rp.cvt_n8 = (size_t)m.K1 * m.d * m.H / 8;
-        rp.cvt_blocks = (int)std::min<size_t>(ceil_div_sz(rp.cvt_n8, 256), (size_t)cu_count() * 2);
     }
     s = launch_route(m, rp, W_router, prototypes, wsplit, reinterpret_cast<float*>(ws + plan.logits), st,
                      reinterpret_cast<uint32_t*>(ws + plan.zero_begin), zwords);
