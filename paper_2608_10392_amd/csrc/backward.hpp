@@ -7,24 +7,11 @@
 // Eq. block-expert-output. The prototypes get none (they only enter TopK).
 //
 // bf16 layers run on the matrix cores (the up and down engines of
-// ffn_bf16.hpp with backward epilogues, and wgrad.hpp); the kernels here
-// serve them for the per-pair and per-token scalars (bwd_weight_kernel,
+// ffn_bf16.hpp with backward epilogues, and wgrad.hpp); the kernels here are
+// the per-pair and per-token scalars (bwd_weight_kernel,
 // bwd_dcoef_sum_kernel, bwd_token_kernel, the router kernels).
-//
-// fp32 layers run on the vector units (fp32 FMA) as tiled fp32 GEMMs over
-// each expert's segment of pairs (rows gathered by token; dense over the H
-// channels, masked to the pair's blocks):
-//   bwd_seg<0>    a = x K^T; act = GELU(a), gp = GELU'(a) on active channels
-//   bwd_seg<1>    E = act V^T                        (per-pair expert output)
-//   bwd_dcoef     dcoef = dy . E                     (d loss / d pair weight)
-//   bwd_seg<2>    dh = dE V, dE = w dy; da = dh gp
-//   bwd_seg<3>    dx_pair = da K
-//   bwd_token     per token: dx = sum of its pairs' dx_pair, plus the router
-//                 terms dz0 W_shr + sum_j dl_j W_j
-//   bwd_wgrad     dW_up[e] = DA_e^T X_e and dW_down[e] = dE_e^T ACT_e over
-//                 the pairs of expert e
-//   bwd_router    dW_router[j] = sum_t dz[t, j] x_t (token slices, then
-//                 their sum)
+// fp32 layers run on the matrix cores in fp32 (ffn_f32.hpp); the kernels here
+// serve both.
 #pragma once
 #include <type_traits>
 
@@ -38,8 +25,6 @@ struct BwdParams {
     float tau, one_minus_2tau;
     const void* X;            // [N, d] layer format
     const void* dY;           // [N, d] layer format
-    const void* Wup;          // [K+1, H, d]
-    const void* Wdown;        // [K+1, d, H]
     const float* Wr;          // [K+1, d]
     const float* alpha;       // routing record
     const int* nres;
@@ -51,28 +36,14 @@ struct BwdParams {
     const int* pair_of;       // [N, K+1]
     const int* seg_off;       // [K+2] first pair of each expert segment
     const int* totals;        // [0]: pairs
-    float* act;               // [pairs, H] GELU(a), zero on inactive channels
-    float* da;                // [pairs, H] GELU'(a), then dL/da; zero on inactive channels
     float* dcoef;             // [pairs] dy . E_pair
     float* pw;                // [pairs] pair weight (alpha or p_i)
-    float* dxp;               // [pairs, d] E_pair, then dx_pair
+    float* dxp;               // [pairs, d] dx_pair
     float* dz;                // [N, K+1]: dz0, then dl_1..dl_K
     float* rpart;             // [kRouterChunks, K+1, d] partial router gradients
     float* dX;                // [N, d]
-    float* dWup;              // [K+1, H, d]
-    float* dWdown;            // [K+1, d, H]
     float* dWr;               // [K+1, d]
 };
-
-__device__ __forceinline__ float ld_f32(const void* p, size_t i) { return static_cast<const float*>(p)[i]; }
-
-
-// Blocks (bit c) that channels [h0, h1) touch, h0 < h1.
-__device__ __forceinline__ uint64_t channel_blocks(int h0, int h1, int M) {
-    const int b0 = h0 / M, b1 = (h1 - 1) / M;
-    const uint64_t hi = (b1 >= 63) ? ~0ull : ((1ull << (b1 + 1)) - 1);
-    return hi & ~((1ull << b0) - 1);
-}
 
 // Weight of pair (t, e): alpha for the shared expert, else the affinity p_i
 // of the residual expert e = q_i.
@@ -91,167 +62,21 @@ __global__ __launch_bounds__(256) void bwd_weight_kernel(BwdParams p) {
         p.pw[pr] = pair_weight(p, p.pair_token[pr], p.pair_expert[pr]);
 }
 
-// dcoef[pr] = dy_{tok(pr)} . E_pr from the partial sums the bf16 path's
-// second up-projection leaves per (pair, block, column half): summed over
-// the blocks of the pair's mask in increasing order (a pair with no block
-// gets 0).
-__global__ __launch_bounds__(256) void bwd_dcoef_sum_kernel(BwdParams p, const float* __restrict__ dcp) {
+// dcoef[pr] = dy_{tok(pr)} . E_pr from the partial sums that the dy V pass
+// leaves per (pair, block), npb of them (bf16 layers: the two column halves;
+// fp32 layers: two per 64-channel chunk): summed over the blocks of the
+// pair's mask in increasing order (a pair with no block gets 0).
+__global__ __launch_bounds__(256) void bwd_dcoef_sum_kernel(BwdParams p, const float* __restrict__ dcp, int npb) {
     const int P = p.totals[0];
     for (int pr = blockIdx.x * blockDim.x + threadIdx.x; pr < P; pr += gridDim.x * blockDim.x) {
         uint64_t m = p.pair_mask[pr];
         float s = 0.f;
         while (m) {
-            const float* q = dcp + ((size_t)pr * p.B + __builtin_ctzll(m)) * 2;
-            s += q[0] + q[1];
+            const float* q = dcp + ((size_t)pr * p.B + __builtin_ctzll(m)) * npb;
+            for (int i = 0; i < npb; i += 2) s += q[i] + q[i + 1];
             m &= m - 1;
         }
         p.dcoef[pr] = s;
-    }
-}
-
-// dcoef[pr] = dy_{tok(pr)} . E_pr, one wave per pair (fp32 path).
-__global__ __launch_bounds__(256) void bwd_dcoef_kernel(BwdParams p) {
-    const int pr = blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (pr >= p.totals[0]) return;
-    const int t = p.pair_token[pr];
-    float s = 0.f;
-    for (int n = lane_id(); n < p.d; n += kWave)
-        s = fmaf(ld_f32(p.dY, (size_t)t * p.d + n), p.dxp[(size_t)pr * p.d + n], s);
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    if (lane_id() == 0) p.dcoef[pr] = s;
-}
-
-// Output tile of the backward GEMMs: kBT x kBT per workgroup of 256
-// threads, kBU x kBU per thread, 16 k per LDS step.
-constexpr int kBT = 128, kBU = kBT / 16;
-
-// C[pr][col] = sum_k L(pr, k) R(k, col) over the pairs of expert e =
-// blockIdx.z, one kBT x kBT tile per workgroup (blockIdx.y: pair tile,
-// blockIdx.x: column tile; tiles past the segment exit).
-//   MODE 0: L = x (k over d), R = K^T (col = channel h)      -> act, gp
-//   MODE 1: L = act (k over H), R = V^T (col = output n)      -> E
-//   MODE 2: L = w dy (k over d), R = V (col = channel h)      -> da = dh gp
-//   MODE 3: L = da (k over H), R = K (col = output n)         -> dx_pair
-template <int MODE>
-__global__ __launch_bounds__(256) void bwd_seg_kernel(BwdParams p) {
-    __shared__ float Ls[16][kBT + 1];
-    __shared__ float Rs[16][kBT + 1];
-    constexpr bool CH = (MODE == 0 || MODE == 2);   // columns are channels
-    constexpr bool KD = (MODE == 0 || MODE == 2);   // contraction over d
-    const int e = blockIdx.z;
-    const int p0 = p.seg_off[e], p1 = p.seg_off[e + 1];
-    const int r0 = p0 + (int)blockIdx.y * kBT;
-    const int cols = CH ? p.H : p.d, kdim = KD ? p.d : p.H;
-    const int c0 = (int)blockIdx.x * kBT;
-    if (r0 >= p1 || c0 >= cols) return;
-    const size_t wu = (size_t)e * p.H * p.d, wd = (size_t)e * p.d * p.H;
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    // Union of the block masks of the tile's pairs. Pairs are sorted by mask
-    // key, so a tile's pairs mostly agree on a block, and a block none of
-    // them runs contributes exact zeros: channel tiles of such blocks are
-    // skipped (MODE 0 writes zeros), and so are k steps inside them.
-    __shared__ uint64_t un_w[kBT / 64];
-    if (threadIdx.x < kBT) {
-        const int pr = r0 + threadIdx.x;
-        uint64_t m = pr < p1 ? p.pair_mask[pr] : 0ull;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) m |= shfl_xor64(m, o);
-        if (lane_id() == 0) un_w[threadIdx.x >> 6] = m;
-    }
-    __syncthreads();
-    uint64_t un = 0;
-#pragma unroll
-    for (int w = 0; w < kBT / 64; ++w) un |= un_w[w];
-    if constexpr (CH) {
-        if ((un & channel_blocks(c0, min(c0 + kBT, cols), p.M)) == 0) {
-            if constexpr (MODE == 0) {
-                for (int i = threadIdx.x; i < kBT * kBT; i += blockDim.x) {
-                    const int pr = r0 + i / kBT, col = c0 + i % kBT;
-                    if (pr < p1 && col < cols) {
-                        p.act[(size_t)pr * p.H + col] = 0.f;
-                        p.da[(size_t)pr * p.H + col] = 0.f;
-                    }
-                }
-            }
-            return;
-        }
-    }
-    float acc[kBU][kBU] = {};
-    for (int k0 = 0; k0 < kdim; k0 += 16) {
-        if constexpr (!KD) {
-            // skip a 16-channel step only if no pair of the tile runs any
-            // block it touches (with M % 16 != 0 a step spans two blocks)
-            if ((un & channel_blocks(k0, min(k0 + 16, kdim), p.M)) == 0) continue;
-        }
-        for (int i = threadIdx.x; i < 16 * kBT; i += blockDim.x) {
-            // L: kBT pair rows x 16 k, consecutive threads along k.
-            {
-                const int r = i / 16, kk = i % 16, pr = r0 + r, k = k0 + kk;
-                float v = 0.f;
-                if (pr < p1 && k < kdim) {
-                    if constexpr (MODE == 0) v = ld_f32(p.X, (size_t)p.pair_token[pr] * p.d + k);
-                    else if constexpr (MODE == 1) v = p.act[(size_t)pr * p.H + k];
-                    else if constexpr (MODE == 2) v = p.pw[pr] * ld_f32(p.dY, (size_t)p.pair_token[pr] * p.d + k);
-                    else v = p.da[(size_t)pr * p.H + k];
-                }
-                Ls[kk][r] = v;
-            }
-            // R: 16 k x kBT columns, consecutive threads along the weight's
-            // contiguous index.
-            {
-                float v = 0.f;
-                if constexpr (MODE == 0 || MODE == 1) {
-                    const int c = i / 16, kk = i % 16, col = c0 + c, k = k0 + kk;
-                    if (col < cols && k < kdim)
-                        v = MODE == 0 ? ld_f32(p.Wup, wu + (size_t)col * p.d + k)       // K_e[h = col][n = k]
-                                      : ld_f32(p.Wdown, wd + (size_t)col * p.H + k);    // V_e[n = col][h = k]
-                    Rs[kk][c] = v;
-                } else {
-                    const int kk = i / kBT, c = i % kBT, col = c0 + c, k = k0 + kk;
-                    if (col < cols && k < kdim)
-                        v = MODE == 2 ? ld_f32(p.Wdown, wd + (size_t)k * p.H + col)     // V_e[n = k][h = col]
-                                      : ld_f32(p.Wup, wu + (size_t)k * p.d + col);      // K_e[h = k][n = col]
-                    Rs[kk][c] = v;
-                }
-            }
-        }
-        __syncthreads();
-#pragma unroll 4
-        for (int kk = 0; kk < 16; ++kk) {
-            float l[kBU], r[kBU];
-#pragma unroll
-            for (int u = 0; u < kBU; ++u) {
-                l[u] = Ls[kk][ty * kBU + u];
-                r[u] = Rs[kk][tx * kBU + u];
-            }
-#pragma unroll
-            for (int u = 0; u < kBU; ++u)
-#pragma unroll
-                for (int v = 0; v < kBU; ++v) acc[u][v] = fmaf(l[u], r[v], acc[u][v]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int u = 0; u < kBU; ++u) {
-        const int pr = r0 + ty * kBU + u;
-        if (pr >= p1) continue;
-        const uint64_t mask = p.pair_mask[pr];
-#pragma unroll
-        for (int v = 0; v < kBU; ++v) {
-            const int col = c0 + tx * kBU + v;
-            if (col >= cols) continue;
-            const float a = acc[u][v];
-            if constexpr (MODE == 0) {
-                const bool on = (mask >> (col / p.M)) & 1ull;
-                p.act[(size_t)pr * p.H + col] = on ? gelu_erf(a) : 0.f;
-                p.da[(size_t)pr * p.H + col] = on ? gelu_grad_erf(a) : 0.f;
-            } else if constexpr (MODE == 2) {
-                float* g = p.da + (size_t)pr * p.H + col;
-                *g = a * *g;
-            } else {
-                p.dxp[(size_t)pr * p.d + col] = a;
-            }
-        }
     }
 }
 
@@ -460,103 +285,6 @@ __global__ __launch_bounds__(256) void bwd_router_sum_kernel(BwdParams p) {
     float s = 0.f;
     for (int c = 0; c < kRouterChunks; ++c) s += p.rpart[(size_t)c * n + item];
     p.dWr[item] = s;
-}
-
-// Weight gradients of expert e as two fp32 GEMMs over its pairs:
-//   dW_up[e][h][n]   = sum_pr da[pr][h] x_{tok(pr)}[n]
-//   dW_down[e][n][h] = sum_pr w_pr dy_{tok(pr)}[n] act[pr][h]
-// blockIdx.z = e, blockIdx.y picks the product (0: up, 1: down); one
-// kBT x kBT output tile per workgroup (rows: h for up, n for down). The sum
-// runs over the tokens in order, 16 per LDS step, each step taking the
-// step's pairs with expert e (a token has at most one), so it is the same on
-// every call (the segment order of the pairs follows the routing kernel's
-// atomics).
-__global__ __launch_bounds__(256) void bwd_wgrad_kernel(BwdParams p, int tiles_h, int tiles_d) {
-    __shared__ float Ls[16][kBT + 1];   // pair x output-row operand
-    __shared__ float Rs[16][kBT + 1];   // pair x output-column operand
-    __shared__ int prs[16];             // the step's pairs with expert e (-1: none)
-    const int e = blockIdx.z, up = blockIdx.y == 0;
-    const int rows = up ? p.H : p.d, cols = up ? p.d : p.H;
-    const int tr = up ? tiles_h : tiles_d, tc = up ? tiles_d : tiles_h;
-    const int tile = blockIdx.x;
-    if (tile >= tr * tc) return;
-    const int r0 = (tile / tc) * kBT, c0 = (tile % tc) * kBT;
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    // Channel blocks of this tile (rows h for up, columns h for down): a
-    // 16-token step whose pairs run none of them adds exact zeros and is
-    // skipped.
-    const uint64_t tmask = up ? channel_blocks(r0, min(r0 + kBT, rows), p.M)
-                              : channel_blocks(c0, min(c0 + kBT, cols), p.M);
-    float acc[kBU][kBU] = {};
-    for (int q0 = 0; q0 < p.N; q0 += 16) {
-        if (threadIdx.x < 16) {
-            const int t = q0 + threadIdx.x;
-            int pr = -1;
-            const int k = t < p.N ? p.nres[t] : 0;
-            if (k > 0) {
-                if (e == 0) {
-                    pr = p.pair_of[(size_t)t * (p.K + 1)];
-                } else {
-                    for (int i = 0; i < k; ++i)
-                        if (p.eids[(size_t)t * p.K + i] == e) {
-                            pr = p.pair_of[(size_t)t * (p.K + 1) + 1 + i];
-                            break;
-                        }
-                }
-            }
-            prs[threadIdx.x] = pr;
-        }
-        __syncthreads();
-        uint64_t cu = 0;
-        for (int j = 0; j < 16; ++j)
-            if (prs[j] >= 0) cu |= p.pair_mask[prs[j]];
-        if ((cu & tmask) == 0) {
-            __syncthreads();   // every thread has read prs before it is rewritten
-            continue;
-        }
-        for (int i = threadIdx.x; i < 16 * kBT; i += blockDim.x) {
-            const int pi = i / kBT, x = i % kBT, pr = prs[pi];
-            float lv = 0.f, rv = 0.f;
-            if (pr >= 0) {
-                const int t = q0 + pi;
-                if (up) {
-                    if (r0 + x < rows) lv = p.da[(size_t)pr * p.H + r0 + x];
-                    if (c0 + x < cols) rv = ld_f32(p.X, (size_t)t * p.d + c0 + x);
-                } else {
-                    if (r0 + x < rows) lv = p.pw[pr] * ld_f32(p.dY, (size_t)t * p.d + r0 + x);
-                    if (c0 + x < cols) rv = p.act[(size_t)pr * p.H + c0 + x];
-                }
-            }
-            Ls[pi][x] = lv;
-            Rs[pi][x] = rv;
-        }
-        __syncthreads();
-#pragma unroll 4
-        for (int pi = 0; pi < 16; ++pi) {
-            float l[kBU], r[kBU];
-#pragma unroll
-            for (int u = 0; u < kBU; ++u) {
-                l[u] = Ls[pi][ty * kBU + u];
-                r[u] = Rs[pi][tx * kBU + u];
-            }
-#pragma unroll
-            for (int u = 0; u < kBU; ++u)
-#pragma unroll
-                for (int v = 0; v < kBU; ++v) acc[u][v] = fmaf(l[u], r[v], acc[u][v]);
-        }
-        __syncthreads();
-    }
-    float* out = up ? p.dWup + (size_t)e * p.H * p.d : p.dWdown + (size_t)e * p.d * p.H;
-#pragma unroll
-    for (int u = 0; u < kBU; ++u) {
-        const int r = r0 + ty * kBU + u;
-        if (r >= rows) continue;
-#pragma unroll
-        for (int v = 0; v < kBU; ++v) {
-            const int c = c0 + tx * kBU + v;
-            if (c < cols) out[(size_t)r * cols + c] = acc[u][v];
-        }
-    }
 }
 
 // Gram diversity loss of the augmented router (Eq. diversity-loss):

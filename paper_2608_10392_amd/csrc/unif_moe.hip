@@ -15,16 +15,17 @@
 //   scatter          pairs (expert segments sorted by block-mask key), the
 //                    per-(expert, block) row lists in token order and the
 //                    up tile table
-//   down_tables      down row tiles and their block-mask unions (bf16)
-//   up, down         block-sparse MFMA grouped GEMMs              (bf16)
-//   pair_ffn_f32     per-pair fp32 FFN                            (fp32)
+//   down_tables      down row tiles and their block-mask unions
+//   up, down         block-sparse MFMA grouped GEMMs, bf16 or fp32
+//                    (fp32 layers past f32_gemm_path's bound: pair_ffn_f32,
+//                    with no tables)
 //   combine          weighted merge in fixed order
 // The block forward adds a LayerNorm pass before routing (pre-LN) and
 // replaces the merge by the block's merge (biases, residual, post-LN). The
 // backward runs routing and the permutation into its workspace, then its
 // own kernels (bf16: weight transposes, the x K^T and dy V passes of the up
 // engine, the dx pass of the down engine, per-token and router kernels and
-// the weight-gradient GEMMs; fp32: vector-unit GEMMs).
+// the weight-gradient GEMMs; fp32: the same passes of the fp32 kernels).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -91,9 +92,19 @@ struct Dims {
     int N, d, K, B, M, H, K1, NL, NLP, lstride, key_bits, nslab, nbin;
     size_t pcap;   // (token, expert) pairs the forward's workspace holds (cfg max_pairs, else N (K+1))
     bool bf16;
+    bool tables;   // slab lists and tile tables are built (all layers but fp32 ones on pair_ffn_f32)
     size_t elem;
     float tau, one_minus_2tau;
 };
+
+// fp32 forwards run on the matrix cores when the activations of every pair of
+// the worst case (or of max_pairs) take at most 8 GiB of workspace; past that
+// the per-pair kernel, which holds one pair's activations in LDS, keeps the
+// workspace what it was (a 1,576-token DeiT-S layer needs 68 MB; the limit is
+// a bound on what a forward may add to a caller's memory, not a crossover:
+// the GEMMs are over 50 times faster at any size).
+constexpr size_t kF32ActBytes = (size_t)8 << 30;
+bool f32_gemm_path(const Dims& m) { return m.pcap * (size_t)m.H * sizeof(float) <= kF32ActBytes; }
 
 Dims dims_of(const unif_moe_config* c) {
     Dims m;
@@ -113,11 +124,16 @@ Dims dims_of(const unif_moe_config* c) {
     const size_t worst = (size_t)m.N * (size_t)m.K1;
     m.pcap = (c->max_pairs > 0 && (size_t)c->max_pairs < worst) ? (size_t)c->max_pairs : worst;
     m.bf16 = c->dtype == UNIF_BF16;
+    m.tables = m.bf16 || f32_gemm_path(m);
     m.elem = m.bf16 ? 2 : 4;
     m.tau = std::isnan(c->tau) ? (float)((double)(m.B - 1) / ((double)m.B * (double)m.B)) : c->tau;
     m.one_minus_2tau = 1.0f - 2.0f * m.tau;
     return m;
 }
+
+// Rows of an up tile and of a down row tile.
+int up_rows(const Dims& m) { return m.bf16 ? up_tm(m.M, m.d) : kF32T; }
+int down_rows(const Dims& m) { return m.bf16 ? down_shape(m.d).tm : kF32T; }
 
 // cfg without a pair capacity (workspaces sized for the worst case).
 unif_moe_config worst_case(unif_moe_config c) {
@@ -249,6 +265,7 @@ struct FwdPlan {
     size_t bin_count, slab_count, exp_total, totals, queues, zero_page, work;
     size_t bin_cursor, seg_off, slab_off, down_tile_off, tile_cnt, max_row_tiles, rt_info, rt_masks;
     size_t pair_token, pair_mask, pair_expert, pair_of, pair_rank, slab_rows, slab_tok, up_tile_info, up_tile_rows, hbuf, part;
+    size_t act;     // fp32 activations of each pair (fp32 layers with tables)
     size_t xn;      // LN(X), the FFN input of a pre-LN block
     size_t wdown16; // fp16 copy of W_down (bf16 layers)
     size_t down_slices; // [kXcds + 1] down tiles per XCD queue
@@ -303,9 +320,9 @@ FwdPlan plan_forward(const Dims& m, size_t xn_bytes = 0) {
     p.slab_off = cv.take(4 * ((size_t)m.nslab + 1));
     p.down_tile_off = cv.take(4 * (K1 + 1));
     p.tile_cnt = cv.take(4 * ceil_div_sz(N, kTileTok) * tile_counters(m));
-    p.max_row_tiles = ceil_div_sz(pmax, kDownTMMin) + K1;
-    p.rt_info = cv.take(m.bf16 ? 16 * p.max_row_tiles : 0);
-    p.rt_masks = cv.take(m.bf16 ? 8 * (kDownTMMax / 32 + 1) * p.max_row_tiles : 0);
+    p.max_row_tiles = ceil_div_sz(pmax, m.bf16 ? kDownTMMin : kF32T) + K1;
+    p.rt_info = cv.take(m.tables ? 16 * p.max_row_tiles : 0);
+    p.rt_masks = cv.take(m.tables ? 8 * (kDownTMMax / 32 + 1) * p.max_row_tiles : 0);
     p.pair_token = cv.take(4 * pmax);
     p.pair_mask = cv.take(8 * (pmax + kDownTMMax));   // a whole down tile is readable past the last pair
     p.pair_expert = cv.take(4 * pmax);
@@ -313,12 +330,13 @@ FwdPlan plan_forward(const Dims& m, size_t xn_bytes = 0) {
     p.pair_rank = cv.take(4 * N * K1);
     // Slab row lists: at most K B rows per token (b + k (B - b) <= K B) and
     // at most B per pair, each slab padded to whole up tiles.
-    const size_t tm = (size_t)up_tm(m.M, m.d);
+    const size_t tm = (size_t)up_rows(m);
     const size_t up_tiles = ceil_div_sz(std::min(N * K, pmax) * (size_t)m.B, tm) + (size_t)m.nslab;
-    p.slab_rows = cv.take(m.bf16 ? 4 * up_tiles * tm : 0);
-    p.slab_tok = cv.take(m.bf16 ? 4 * up_tiles * tm : 0);
-    p.up_tile_info = cv.take(m.bf16 ? 4 * up_tiles : 0);
-    p.up_tile_rows = cv.take(m.bf16 ? 4 * up_tiles : 0);
+    p.slab_rows = cv.take(m.tables ? 4 * up_tiles * tm : 0);
+    p.slab_tok = cv.take(m.tables ? 4 * up_tiles * tm : 0);
+    p.up_tile_info = cv.take(m.tables ? 4 * up_tiles : 0);
+    p.up_tile_rows = cv.take(m.tables ? 4 * up_tiles : 0);
+    p.act = cv.take(!m.bf16 && m.tables ? pmax * (size_t)m.H * sizeof(float) : 0);
     p.hbuf = cv.take(m.bf16 ? (pmax + 1) * (size_t)m.H * 2 : 0);  // fp16, + the sink row
     p.part = cv.take((pmax + 1) * (size_t)m.d * sizeof(float) * down_splits(m));   // fp32, + the sink row, per part
     p.xn = cv.take(xn_bytes);
@@ -574,12 +592,53 @@ int32_t launch_up(const Dims& m, int grid, size_t lds, hipStream_t st, const UpP
     }
 }
 
+// The fp32 kernels' view of a workspace, and their grid: persistent over the
+// device's tile counts, as many workgroups as fit at once (4 per compute unit
+// by LDS).
+F32Params f32_params(const Dims& m, const FwdPlan& plan, char* ws, const void* X, const void* W_up,
+                     const void* W_down) {
+    F32Params f = {};
+    f.d = m.d;
+    f.M = m.M;
+    f.B = m.B;
+    f.H = m.H;
+    f.X = static_cast<const float*>(X);
+    f.Wup = static_cast<const float*>(W_up);
+    f.Wdown = static_cast<const float*>(W_down);
+    f.act = reinterpret_cast<float*>(ws + plan.act);
+    f.part = reinterpret_cast<float*>(ws + plan.part);
+    f.slab_rows = reinterpret_cast<const int*>(ws + plan.slab_rows);
+    f.slab_tok = reinterpret_cast<const int*>(ws + plan.slab_tok);
+    f.tile_info = reinterpret_cast<const int*>(ws + plan.up_tile_info);
+    f.tile_rows = reinterpret_cast<const int*>(ws + plan.up_tile_rows);
+    f.totals = reinterpret_cast<const int*>(ws + plan.totals);
+    f.rt_info = reinterpret_cast<const int4*>(ws + plan.rt_info);
+    f.rt_masks = reinterpret_cast<const uint64_t*>(ws + plan.rt_masks);
+    f.pair_mask = reinterpret_cast<const uint64_t*>(ws + plan.pair_mask);
+    f.slab_off = reinterpret_cast<const int*>(ws + plan.slab_off);
+    f.slab_count = reinterpret_cast<const int*>(ws + plan.slab_count);
+    return f;
+}
+unsigned f32_grid(int cus) { return (unsigned)cus * 4; }
+
+// kTables: stop after the permutation (the backward's front part).
+// kNoTables: the forward of an fp32 layer on the per-pair kernel, whatever
+// f32_gemm_path says (it needs the least workspace).
+enum class Run { kForward, kTables, kNoTables };
+
+Dims dims_for(const unif_moe_config* c, Run run) {
+    Dims m = dims_of(c);
+    if (run == Run::kTables) m.tables = true;
+    if (run == Run::kNoTables) m.tables = m.bf16;
+    return m;
+}
+
 // The layer forward (blk == nullptr) or the block forward around it.
 int32_t forward_impl(const unif_moe_config* cfg, const unif_moe_block* blk, const void* X,
                      const uint8_t* valid, const float* W_router, const float* prototypes,
                      const void* W_up, const void* W_down, void* Y,
                      const unif_moe_routing* routing_out, void* workspace, size_t workspace_bytes,
-                     void* const* events, void* stream, bool tables_only = false) {
+                     void* const* events, void* stream, Run run = Run::kForward) {
     int32_t s = check_config(cfg);
     if (s != UNIF_OK) return s;
     s = check_forward_shape(cfg);
@@ -592,16 +651,14 @@ int32_t forward_impl(const unif_moe_config* cfg, const unif_moe_block* blk, cons
     }
     if (routing_out != nullptr && !record_complete(routing_out)) return UNIF_EINVAL;
     if (cfg->n_tokens > 0 && (X == nullptr || W_router == nullptr || prototypes == nullptr ||
-                              W_up == nullptr || W_down == nullptr || (Y == nullptr && !tables_only)))
+                              W_up == nullptr || W_down == nullptr || (Y == nullptr && run != Run::kTables)))
         return UNIF_EINVAL;
-    const Dims m = dims_of(cfg);
+    const bool tables_only = run == Run::kTables;
+    const Dims m = dims_for(cfg, run);
     const bool own = routing_out == nullptr;
+    // The plan always includes the internal record.
     const FwdPlan plan = plan_forward(m, block_xn_bytes(cfg, blk));
-    // The size reported by the query always includes the internal record.
-    size_t need = 0;
-    if (blk != nullptr) unif_moe_block_forward_workspace_size(cfg, blk, &need);
-    else unif_moe_layer_forward_workspace_size(cfg, &need);
-    if (workspace == nullptr || workspace_bytes < need) return UNIF_EWORKSPACE;
+    if (workspace == nullptr || workspace_bytes < plan.total) return UNIF_EWORKSPACE;
     if (m.N == 0) return UNIF_OK;
 
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -666,9 +723,9 @@ int32_t forward_impl(const unif_moe_config* cfg, const unif_moe_block* blk, cons
     pp.B = m.B;
     pp.key_bits = m.key_bits;
     const DownShape dsh = down_shape(m.d);
-    pp.bm_up = up_tm(m.M, m.d);
+    pp.bm_up = up_rows(m);
     pp.up_group = up_block_group(m.d, m.M, m.B);
-    pp.bm_down = dsh.tm;
+    pp.bm_down = down_rows(m);
     pp.down_col_tiles = m.bf16 ? m.d / dsh.bn : 1;
     pp.mask = mask;
     pp.nres = nres;
@@ -684,27 +741,27 @@ int32_t forward_impl(const unif_moe_config* cfg, const unif_moe_block* blk, cons
     pp.pair_mask = reinterpret_cast<uint64_t*>(ws + plan.pair_mask);
     pp.pair_expert = reinterpret_cast<int*>(ws + plan.pair_expert);
     pp.pair_of = reinterpret_cast<int*>(ws + plan.pair_of);
-    pp.slab_rows = m.bf16 ? reinterpret_cast<int*>(ws + plan.slab_rows) : nullptr;
-    pp.slab_tok = m.bf16 ? reinterpret_cast<int*>(ws + plan.slab_tok) : nullptr;
-    pp.up_tile_info = m.bf16 ? reinterpret_cast<int*>(ws + plan.up_tile_info) : nullptr;
-    pp.up_tile_rows = m.bf16 ? reinterpret_cast<int*>(ws + plan.up_tile_rows) : nullptr;
+    pp.slab_rows = m.tables ? reinterpret_cast<int*>(ws + plan.slab_rows) : nullptr;
+    pp.slab_tok = m.tables ? reinterpret_cast<int*>(ws + plan.slab_tok) : nullptr;
+    pp.up_tile_info = m.tables ? reinterpret_cast<int*>(ws + plan.up_tile_info) : nullptr;
+    pp.up_tile_rows = m.tables ? reinterpret_cast<int*>(ws + plan.up_tile_rows) : nullptr;
     pp.tile_cnt = reinterpret_cast<int*>(ws + plan.tile_cnt);
     pp.exp_total = rp.exp_total;
-    pp.rt_info = m.bf16 ? reinterpret_cast<int4*>(ws + plan.rt_info) : nullptr;
-    pp.rt_masks = m.bf16 ? reinterpret_cast<uint64_t*>(ws + plan.rt_masks) : nullptr;
+    pp.rt_info = m.tables ? reinterpret_cast<int4*>(ws + plan.rt_info) : nullptr;
+    pp.rt_masks = m.tables ? reinterpret_cast<uint64_t*>(ws + plan.rt_masks) : nullptr;
     pp.pair_rank = rp.pair_rank;
     pp.ntile = ceil_div(m.N, kTileTok);
     pp.max_pairs = (int)m.pcap;
     pp.down_slices = reinterpret_cast<int*>(ws + plan.down_slices);
-    pp.down_stages = m.M / 64;
+    pp.down_stages = m.M / 64;   // bf16
     // The backward (tables_only) runs its down-projection unsplit.
     pp.down_splits = tables_only ? 1 : down_splits(m);
-    // Expert segments and bin cursors; per slab (bf16), its rows per token
-    // tile as first rows.
-    scan_kernel<<<(unsigned)(m.K1 + (m.bf16 ? m.nslab : 0)), kScanThreads, 0, st>>>(pp);
+    // Expert segments and bin cursors; per slab, its rows per token tile as
+    // first rows.
+    scan_kernel<<<(unsigned)(m.K1 + (m.tables ? m.nslab : 0)), kScanThreads, 0, st>>>(pp);
     UNIF_LAUNCH_CHECK();
-    // Pairs and slab rows; the up tile table (bf16).
-    const int up_groups = m.bf16 ? m.K1 * ceil_div(m.B, pp.up_group) : 0;
+    // Pairs and slab rows; the up tile table.
+    const int up_groups = m.tables ? m.K1 * ceil_div(m.B, pp.up_group) : 0;
     {
         const size_t lds = scatter_lds_bytes(m);
         if (allow_lds(scatter_kernel, lds) != UNIF_OK) return UNIF_EDEVICE;
@@ -715,12 +772,14 @@ int32_t forward_impl(const unif_moe_config* cfg, const unif_moe_block* blk, cons
 
     const int cus = cu_count();
     void* part = ws + plan.part;
-    if (m.bf16) {
+    if (m.tables) {
         // Down row-tile descriptions (the grid-stride loop is sized for the
         // worst case only up to a few workgroups per CU).
         down_tables_kernel<<<(unsigned)std::min<size_t>(ceil_div_sz(plan.max_row_tiles, 4), (size_t)cus * 4), 256, 0,
                              st>>>(pp);
         UNIF_LAUNCH_CHECK();
+    }
+    if (m.bf16) {
         // The down tiles of each XCD's queue, split by cost.
         down_slices_kernel<<<1, kSliceThreads, 0, st>>>(pp);
         UNIF_LAUNCH_CHECK();
@@ -782,6 +841,16 @@ int32_t forward_impl(const unif_moe_config* cfg, const unif_moe_block* blk, cons
     } else {
         UNIF_MARK(3);
         if (tables_only) return UNIF_OK;
+        if (m.tables) {
+            F32Params fp = f32_params(m, plan, ws, Xf, W_up, W_down);
+            fp.b_up = blk != nullptr ? blk->b_up : nullptr;
+            f32_up_kernel<kF32Gelu><<<f32_grid(cus), 256, 0, st>>>(fp);
+            UNIF_LAUNCH_CHECK();
+            UNIF_MARK(4);
+            f32_down_kernel<false><<<f32_grid(cus), 256, 0, st>>>(fp);
+            UNIF_LAUNCH_CHECK();
+            UNIF_MARK(5);
+        } else {
         PairF32Params fp;
         fp.d = m.d;
         fp.M = m.M;
@@ -802,6 +871,7 @@ int32_t forward_impl(const unif_moe_config* cfg, const unif_moe_block* blk, cons
         UNIF_LAUNCH_CHECK();
         UNIF_MARK(4);
         UNIF_MARK(5);
+        }
     }
 
     // 5. weighted merge (the block's merge around it)
@@ -931,11 +1001,11 @@ namespace {
 // Backward workspace: the forward's (routing record, pair tables, slab
 // lists; for bf16 layers its H buffer holds GELU(a), then w GELU(a), and its
 // fp16 W_down region the transposed W_up; its per-pair rows receive dx_pair),
-// then for bf16 layers a second H-shaped buffer (GELU'(a), then d loss / da),
-// V^T and the per-(pair, block) partial sums of dy . E, for fp32 layers the
-// per-pair fp32 intermediates, and the per-pair and per-token scalars.
+// then a second H-shaped buffer (GELU'(a), then d loss / da; fp32 for fp32
+// layers), for bf16 layers V^T, the per-(pair, block) partial sums of dy . E
+// and the per-pair and per-token scalars.
 struct BwdPlan {
-    size_t fwd, act, da, gbuf, wdnT, dcp, dcoef, pw, dz, rpart, queues, total;
+    size_t fwd, da, gbuf, wdnT, dcp, dcoef, pw, dz, rpart, queues, total;
 };
 
 BwdPlan plan_backward(const Dims& m) {
@@ -944,11 +1014,10 @@ BwdPlan plan_backward(const Dims& m) {
     const size_t pmax = (size_t)m.N * m.K1;
     Carver cv;
     cv.cur = b.fwd;
-    b.act = cv.take(m.bf16 ? 0 : pmax * m.H * sizeof(float));
     b.da = cv.take(m.bf16 ? 0 : pmax * m.H * sizeof(float));
     b.gbuf = cv.take(m.bf16 ? (pmax + 1) * (size_t)m.H * 2 : 0);   // + the sink row
     b.wdnT = cv.take(m.bf16 ? (size_t)m.K1 * m.d * m.H * 2 : 0);
-    b.dcp = cv.take(m.bf16 ? (pmax + 1) * m.B * 2 * sizeof(float) : 0);
+    b.dcp = cv.take(m.bf16 ? (pmax + 1) * m.B * 2 * sizeof(float) : pmax * f32_partials(m.B, m.M) * sizeof(float));
     b.dcoef = cv.take(pmax * sizeof(float));
     b.pw = cv.take(pmax * sizeof(float));
     b.dz = cv.take((size_t)m.N * m.K1 * sizeof(float));
@@ -958,13 +1027,14 @@ BwdPlan plan_backward(const Dims& m) {
     return b;
 }
 
+constexpr int kF32BackwardMaxTokens = 8388480;   // the documented bound
+
 int32_t check_backward_shape(const unif_moe_config* c) {
     int32_t s = check_config(c);
     if (s != UNIF_OK) return s;
     s = check_forward_shape(c);
     if (s != UNIF_OK) return s;
-    // fp32 layers: pair tiles of an expert segment index grid dimension y.
-    if (c->dtype == UNIF_F32 && ceil_div(c->n_tokens, kBT) > 65535) return UNIF_EUNSUPPORTED;
+    if (c->dtype == UNIF_F32 && c->n_tokens > kF32BackwardMaxTokens) return UNIF_EUNSUPPORTED;
     // the per-token and router-gradient kernels take 4 and 8 columns at a time
     if (c->d_model % 8 != 0) return UNIF_EUNSUPPORTED;
     return UNIF_OK;
@@ -1007,7 +1077,7 @@ int32_t unif_moe_layer_backward_workspace_size(const unif_moe_config* cfg, size_
     const int32_t s = check_backward_shape(cfg);
     if (s != UNIF_OK) return s;
     const unif_moe_config cw = worst_case(*cfg);
-    *bytes = plan_backward(dims_of(&cw)).total;
+    *bytes = plan_backward(dims_for(&cw, Run::kTables)).total;
     return UNIF_OK;
 }
 
@@ -1023,7 +1093,7 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
                               W_down == nullptr || dY == nullptr || dX == nullptr))
         return UNIF_EINVAL;
     if (dW_up == nullptr || dW_down == nullptr || dW_router == nullptr) return UNIF_EINVAL;
-    const Dims m = dims_of(cfg);
+    const Dims m = dims_for(cfg, Run::kTables);
     const BwdPlan bp = plan_backward(m);
     if (workspace == nullptr || workspace_bytes < bp.total) return UNIF_EWORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -1040,19 +1110,15 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
     p.one_minus_2tau = m.one_minus_2tau;
     p.X = X;
     p.dY = dY;
-    p.Wup = W_up;
-    p.Wdown = W_down;
     p.Wr = W_router;
     p.dX = dX;
-    p.dWup = dW_up;
-    p.dWdown = dW_down;
     p.dWr = dW_router;
     // 1. routing and the permutation's tables into the front of the workspace
     char* ws = align_base(workspace);
     const FwdPlan fp = plan_forward(m);
     if (m.N > 0) {
         s = forward_impl(cfg, nullptr, X, valid, W_router, prototypes, W_up, W_down, nullptr, nullptr, ws,
-                         bp.fwd, nullptr, stream, true);
+                         bp.fwd, nullptr, stream, Run::kTables);
         if (s != UNIF_OK) return s;
     }
     p.alpha = reinterpret_cast<const float*>(ws + fp.alpha);
@@ -1065,8 +1131,6 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
     p.pair_of = reinterpret_cast<const int*>(ws + fp.pair_of);
     p.seg_off = reinterpret_cast<const int*>(ws + fp.seg_off);
     p.totals = reinterpret_cast<const int*>(ws + fp.totals);
-    p.act = reinterpret_cast<float*>(ws + bp.act);
-    p.da = reinterpret_cast<float*>(ws + bp.da);
     p.dcoef = reinterpret_cast<float*>(ws + bp.dcoef);
     p.pw = reinterpret_cast<float*>(ws + bp.pw);
     p.rpart = reinterpret_cast<float*>(ws + bp.rpart);
@@ -1088,6 +1152,8 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
     const size_t pmax = (size_t)m.N * m.K1;
     u16* const abuf = reinterpret_cast<u16*>(ws + fp.hbuf);
     u16* const gbuf = reinterpret_cast<u16*>(ws + bp.gbuf);
+    float* const dcp = reinterpret_cast<float*>(ws + bp.dcp);
+    F32Params f;
     if (m.bf16) {
         // 2. V^T [K+1, H, d] (rows of dy V as the up kernel's weights) and
         //    K^T [K+1, d, H] (dx_pair = da K as the down kernel's weights)
@@ -1122,7 +1188,6 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
         up.b_up = nullptr;
         up.Gbuf = gbuf;
         up.pw = p.pw;
-        float* const dcp = reinterpret_cast<float*>(ws + bp.dcp);
         up.dcp = dcp;
         up.sink_row = (int)pmax;
         const size_t up_lds = (size_t)up_lds_bytes(m.M, up_tm(m.M, m.d));
@@ -1134,7 +1199,7 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
         up.queue = queues + 8;
         s = launch_up<kEpiDa>(m, grid, up_lds, st, up);
         if (s != UNIF_OK) return s;
-        bwd_dcoef_sum_kernel<<<(unsigned)cus * 4, 256, 0, st>>>(p, dcp);
+        bwd_dcoef_sum_kernel<<<(unsigned)cus * 4, 256, 0, st>>>(p, dcp, 2);
         UNIF_LAUNCH_CHECK();
         // 4. dx_pair = da K over each pair's blocks
         const DownShape dsh = down_shape(m.d);
@@ -1164,16 +1229,16 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
             s = launch_persistent(down_kernel<4, 2, false>, grid, (size_t)down_lds_bytes(256, 128), st, dn);
         if (s != UNIF_OK) return s;
     } else {
-        // 2. per pair: tiled fp32 GEMMs over each expert's segment
-        const int tiles_h = ceil_div(m.H, kBT), tiles_d = ceil_div(m.d, kBT);
-        const unsigned ptiles = (unsigned)ceil_div(m.N, kBT);
-        const dim3 g_ch((unsigned)tiles_h, ptiles, (unsigned)m.K1), g_out((unsigned)tiles_d, ptiles, (unsigned)m.K1);
-        const unsigned gp = (unsigned)ceil_div(m.N * m.K1, 4);
-        bwd_seg_kernel<0><<<g_ch, 256, 0, st>>>(p);
-        bwd_seg_kernel<1><<<g_out, 256, 0, st>>>(p);
-        bwd_dcoef_kernel<<<gp, 256, 0, st>>>(p);
-        bwd_seg_kernel<2><<<g_ch, 256, 0, st>>>(p);
-        bwd_seg_kernel<3><<<g_out, 256, 0, st>>>(p);
+        // 2. the same products in fp32: a = x K^T, dy V, dx_pair = da K
+        f = f32_params(m, fp, ws, X, W_up, W_down);
+        f.dY = static_cast<const float*>(dY);
+        f.da = reinterpret_cast<float*>(ws + bp.da);
+        f.dcp = dcp;
+        f.pw = p.pw;
+        f32_up_kernel<kF32Pre><<<f32_grid(cus), 256, 0, st>>>(f);
+        f32_up_kernel<kF32Da><<<f32_grid(cus), 256, 0, st>>>(f);
+        bwd_dcoef_sum_kernel<<<(unsigned)cus * 4, 256, 0, st>>>(p, dcp, 2 * f32_chunks(m.M));
+        f32_down_kernel<true><<<f32_grid(cus), 256, 0, st>>>(f);
         UNIF_LAUNCH_CHECK();
     }
     // 5. per token: dX and the router-logit gradients; the router's weight gradient
@@ -1208,9 +1273,11 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
         s = launch_wgrad<false>(w, m.nslab, st);
         if (s != UNIF_OK) return s;
     } else {
-        const int tiles_h = ceil_div(m.H, kBT), tiles_d = ceil_div(m.d, kBT);
-        const dim3 wg_grid((unsigned)(tiles_h * tiles_d), 2, (unsigned)m.K1);
-        bwd_wgrad_kernel<<<wg_grid, 256, 0, st>>>(p, tiles_h, tiles_d);
+        const unsigned g = (unsigned)(m.nslab * f32_chunks(m.M) * ceil_div(m.d, kF32T));
+        f.dW = dW_up;
+        f32_wgrad_kernel<true><<<g, 256, 0, st>>>(f);
+        f.dW = dW_down;
+        f32_wgrad_kernel<false><<<g, 256, 0, st>>>(f);
         UNIF_LAUNCH_CHECK();
     }
     return UNIF_OK;
@@ -1352,12 +1419,17 @@ int32_t unif_moe_layer_forward_static(const unif_moe_config* cfg, const void* X,
     size_t need = 0;
     const int32_t s = unif_moe_layer_forward_workspace_size(cfg, &need);
     if (s != UNIF_OK) return s;
-    if (need > kStaticScratchBytes) return UNIF_EWORKSPACE;
+    // fp32 layers whose activations do not fit run on the per-pair kernel.
+    Run run = Run::kForward;
+    if (need > kStaticScratchBytes) {
+        run = Run::kNoTables;
+        if (plan_forward(dims_for(cfg, run)).total > kStaticScratchBytes) return UNIF_EWORKSPACE;
+    }
     void* ws = nullptr;
     const int32_t e = static_scratch(&ws);
     if (e != UNIF_OK) return e;
     return forward_impl(cfg, nullptr, X, valid, W_router, prototypes, W_up, W_down, Y, routing_out, ws,
-                        kStaticScratchBytes, nullptr, stream);
+                        kStaticScratchBytes, nullptr, stream, run);
 }
 
 }  // extern "C"
