@@ -1005,7 +1005,9 @@ namespace {
 // layers), for bf16 layers V^T, the per-(pair, block) partial sums of dy . E
 // and the per-pair and per-token scalars.
 struct BwdPlan {
-    size_t fwd, da, gbuf, wdnT, dcp, dcoef, pw, dz, rpart, queues, total;
+    size_t fwd, da, gbuf, wdnT, dcp, dcoef, pw, dz, rpart, queues, units, split, total;
+    int extra;   // units of the weight gradients on top of one per slab, at most
+    int slots;   // partial sums of split weight-gradient slabs that fit the per-pair rows' region
 };
 
 BwdPlan plan_backward(const Dims& m) {
@@ -1023,6 +1025,12 @@ BwdPlan plan_backward(const Dims& m) {
     b.dz = cv.take((size_t)m.N * m.K1 * sizeof(float));
     b.rpart = cv.take((size_t)kRouterChunks * m.K1 * m.d * sizeof(float));
     b.queues = cv.take(4 * 32);
+    // The weight gradients' units; their partial sums take the place of the
+    // per-pair rows, which are done with by then.
+    b.slots = m.bf16 ? (int)std::min<size_t>(pmax / (2 * m.M), (size_t)1 << 16) : 0;   // for each of the two gradients
+    b.extra = m.bf16 ? ceil_div(512, m.d % 256 == 0 ? m.d / 256 : m.d / 128) : 0;   // 512 tiles: two per compute unit
+    b.units = cv.take(m.bf16 ? 16 * ((size_t)m.nslab + b.extra) : 0);
+    b.split = cv.take(m.bf16 ? 8 * (size_t)m.nslab : 0);
     b.total = cv.cur + 256;
     return b;
 }
@@ -1042,30 +1050,30 @@ int32_t check_backward_shape(const unif_moe_config* c) {
 
 // The weight-gradient launch for block width M and n tiles of TN columns.
 template <bool UP, int GQ, int GP, int WQ>
-int32_t launch_wgrad1(const WgradParams& w, int nslab, hipStream_t st) {
+int32_t launch_wgrad1(const WgradParams& w, int n_units, hipStream_t st) {
     constexpr int TQ = WQ * GQ * 32, TP = (8 / WQ) * GP * 32;
     const size_t lds = (size_t)wgrad_lds_bytes(TQ, TP);
     if (allow_lds(wgrad_kernel<UP, GQ, GP, WQ>, lds) != UNIF_OK) return UNIF_EDEVICE;
-    wgrad_kernel<UP, GQ, GP, WQ><<<(unsigned)(nslab * w.ntn), 512, lds, st>>>(w);
+    wgrad_kernel<UP, GQ, GP, WQ><<<(unsigned)(n_units * w.ntn), 512, lds, st>>>(w);
     return hipGetLastError() == hipSuccess ? UNIF_OK : UNIF_EDEVICE;
 }
 
 template <bool UP, int GN>
-int32_t launch_wgrad_m(const WgradParams& w, int nslab, hipStream_t st) {
+int32_t launch_wgrad_m(const WgradParams& w, int n_units, hipStream_t st) {
     // dW_up: Q = h (2 waves x M / 64 groups), P = n (4 waves x GN groups);
     // dW_down: Q = n (4 waves x GN groups), P = h (2 waves x M / 64 groups).
     switch (w.M / 64) {
-        case 1: return UP ? launch_wgrad1<true, 1, GN, 2>(w, nslab, st) : launch_wgrad1<false, GN, 1, 4>(w, nslab, st);
-        case 2: return UP ? launch_wgrad1<true, 2, GN, 2>(w, nslab, st) : launch_wgrad1<false, GN, 2, 4>(w, nslab, st);
-        case 3: return UP ? launch_wgrad1<true, 3, GN, 2>(w, nslab, st) : launch_wgrad1<false, GN, 3, 4>(w, nslab, st);
-        case 4: return UP ? launch_wgrad1<true, 4, GN, 2>(w, nslab, st) : launch_wgrad1<false, GN, 4, 4>(w, nslab, st);
+        case 1: return UP ? launch_wgrad1<true, 1, GN, 2>(w, n_units, st) : launch_wgrad1<false, GN, 1, 4>(w, n_units, st);
+        case 2: return UP ? launch_wgrad1<true, 2, GN, 2>(w, n_units, st) : launch_wgrad1<false, GN, 2, 4>(w, n_units, st);
+        case 3: return UP ? launch_wgrad1<true, 3, GN, 2>(w, n_units, st) : launch_wgrad1<false, GN, 3, 4>(w, n_units, st);
+        case 4: return UP ? launch_wgrad1<true, 4, GN, 2>(w, n_units, st) : launch_wgrad1<false, GN, 4, 4>(w, n_units, st);
         default: return UNIF_EUNSUPPORTED;
     }
 }
 
 template <bool UP>
-int32_t launch_wgrad(const WgradParams& w, int nslab, hipStream_t st) {
-    return w.ntn * 256 == w.d ? launch_wgrad_m<UP, 2>(w, nslab, st) : launch_wgrad_m<UP, 1>(w, nslab, st);
+int32_t launch_wgrad(const WgradParams& w, int n_units, hipStream_t st) {
+    return w.ntn * 256 == w.d ? launch_wgrad_m<UP, 2>(w, n_units, st) : launch_wgrad_m<UP, 1>(w, n_units, st);
 }
 
 }  // namespace
@@ -1262,16 +1270,36 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
         w.slab_tok = reinterpret_cast<const int*>(ws + fp.slab_tok);
         w.slab_off = reinterpret_cast<const int*>(ws + fp.slab_off);
         w.slab_count = reinterpret_cast<const int*>(ws + fp.slab_count);
+        WgradUnitParams wu;
+        wu.nslab = m.nslab;
+        wu.ntn = w.ntn;
+        wu.cus = cus;
+        wu.slots = bp.slots;
+        wu.extra = bp.extra;
+        wu.slab_count = w.slab_count;
+        wu.units = reinterpret_cast<int4*>(ws + bp.units);
+        wu.split = reinterpret_cast<int2*>(ws + bp.split);
+        wgrad_units_kernel<<<1, kWgradUnitThreads, 0, st>>>(wu);
+        UNIF_LAUNCH_CHECK();
+        w.units = wu.units;
+        w.partial = p.dxp;
         w.Psrc = static_cast<const u16*>(X);
         w.Qsrc = gbuf;
         w.out = dW_up;
-        s = launch_wgrad<true>(w, m.nslab, st);
+        s = launch_wgrad<true>(w, m.nslab + bp.extra, st);
         if (s != UNIF_OK) return s;
+        const WgradParams w_up = w;
+        w.partial = p.dxp + (size_t)bp.slots * m.M * m.d;
         w.Psrc = abuf;
         w.Qsrc = static_cast<const u16*>(dY);
         w.out = dW_down;
-        s = launch_wgrad<false>(w, m.nslab, st);
+        s = launch_wgrad<false>(w, m.nslab + bp.extra, st);
         if (s != UNIF_OK) return s;
+        if (bp.slots > 0) {
+            const dim3 sgrid((unsigned)std::min(ceil_div(m.M * m.d / 4, 256), 16), (unsigned)m.nslab, 2);
+            wgrad_sum_kernel<<<sgrid, 256, 0, st>>>(w_up, w, wu.split);
+            UNIF_LAUNCH_CHECK();
+        }
     } else {
         const unsigned g = (unsigned)(m.nslab * f32_chunks(m.M) * ceil_div(m.d, kF32T));
         f.dW = dW_up;

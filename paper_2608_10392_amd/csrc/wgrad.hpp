@@ -17,6 +17,14 @@
 // stage s is multiplied, the rows of stage s + 2 and the list indices of
 // stage s + 3 are in flight.
 //
+// The shared expert's slabs are several times longer than the residual ones
+// (DeiT-S, 18,912 tokens: 148 stages against 50, and 168 tiles in all), so
+// long slabs are split by rows into units (wgrad_units_kernel), whose partial
+// sums are added in row order by wgrad_sum_kernel. One workgroup per unit and
+// n tile. (Persistent workgroups taking the tiles from a queue, and per-XCD
+// runs of them in token order, were slower: 56 -> 70 us per gradient on the
+// padded BERT-base batch, 690 -> 800 us on vit_b16.)
+//
 // Output tile TQ x TP per workgroup of 8 waves (WQ x WP), where P is the
 // output's contiguous index (n for dW_up, h for dW_down) and Q the other.
 // P is the MFMA A operand, stored in LDS in wcol order, so each lane
@@ -24,6 +32,7 @@
 #pragma once
 #include "common.hpp"
 #include "ffn_bf16.hpp"
+#include "permute.hpp"
 
 namespace unifmoe {
 
@@ -37,7 +46,83 @@ struct WgradParams {
     const int* slab_off;      // first row of each slab in the lists (a multiple of 64)
     const int* slab_count;    // rows of each slab
     float* out;               // dW_up [K+1, H, d] or dW_down [K+1, d, H]
+    const int4* units;        // slab, first row, rows, partial slot (-1: the whole slab, straight to out)
+    float* partial;           // [slots][M d] partial sums, each in the layout of its tile of out
 };
+
+// Units of the slabs' row lists, in slab order. The rows per unit are sized on
+// the device from the slabs' counts: 5/4 of a compute unit's even share of all
+// stages (so that a call whose units would all fit at once has no second
+// round), at least kWgradMinStages (a unit's partial sums cost about as much
+// as 8 stages), and so that no more than `extra` units come on top of one per
+// slab and the partial sums fit `slots`. DeiT-S then splits its shared slabs
+// in three (50 stages on the longest compute unit against 148: both gradients
+// 328 -> 173 us with the sums); vit_b16 (394 stages against an even share of 323) and
+// the padded BERT-base batch split none.
+constexpr int kWgradMinStages = 24;
+constexpr int kWgradUnitThreads = 1024;
+struct WgradUnitParams {
+    int nslab, ntn, cus, slots, extra;
+    const int* slab_count;
+    int4* units;              // [nslab + extra]; those past the last have slab -1
+    int2* split;              // [nslab]: first partial slot, parts (1: none)
+};
+
+__global__ __launch_bounds__(kWgradUnitThreads) void wgrad_units_kernel(WgradUnitParams p) {
+    __shared__ int lds[kWgradUnitThreads / 64];
+    const int tid = threadIdx.x, T = blockDim.x;
+    const int per = ceil_div(p.nslab, T), s0 = min(p.nslab, tid * per), s1 = min(p.nslab, s0 + per);
+    auto stages = [&](int s) { return ceil_div(p.slab_count[s], Stage::SK); };
+    int n = 0;
+    for (int s = s0; s < s1; ++s) n += stages(s);
+    int all;
+    block_prefix(n, lds, all);
+    int unit = max(kWgradMinStages, (int)((int64_t)all * p.ntn * 5 / ((int64_t)p.cus * 4)));
+    // The slabs take at most nslab + all / unit units; a split slab takes
+    // ceil(stages / unit) <= 2 stages / unit slots.
+    unit = max(unit, max(ceil_div(all, max(p.extra, 1)), ceil_div(2 * all, max(p.slots, 1))));
+    auto parts = [&](int s) { return max(1, ceil_div(stages(s), unit)); };
+    int nu = 0, ns = 0;
+    for (int s = s0; s < s1; ++s) {
+        const int q = parts(s);
+        nu += q;
+        ns += q > 1 ? q : 0;
+    }
+    int n_units, n_slots;
+    int u = block_prefix(nu, lds, n_units), slot = block_prefix(ns, lds, n_slots);
+    for (int s = s0; s < s1; ++s) {
+        const int q = parts(s), cnt = p.slab_count[s], rows = ceil_div(stages(s), q) * Stage::SK;
+        p.split[s] = make_int2(slot, q);
+        for (int i = 0; i < q; ++i) {
+            // the last part may be empty when the parts are rounded up to stages
+            const int r0 = min(cnt, i * rows);
+            p.units[u++] = make_int4(s, r0, min(rows, cnt - r0), q > 1 ? slot + i : -1);
+        }
+        slot += q > 1 ? q : 0;
+    }
+    for (int x = n_units + tid; x < p.nslab + p.extra; x += T) p.units[x] = make_int4(-1, 0, 0, -1);
+}
+
+// out = the partial sums of every split slab, added in row order; one thread
+// per four elements, both gradients (blockIdx.z) in one launch. A slab's tile of out is R rows of C (dW_up: M x d, dW_down:
+// d x M).
+__global__ __launch_bounds__(256) void wgrad_sum_kernel(WgradParams up, WgradParams down, const int2* __restrict__ split) {
+    const int slab = blockIdx.y;
+    const int2 sp = split[slab];
+    if (sp.y <= 1) return;
+    const bool UP = blockIdx.z == 0;
+    const WgradParams& p = UP ? up : down;
+    const int e = slab / p.B, c = slab - e * p.B, C4 = (UP ? p.d : p.M) / 4, n4 = p.M * p.d / 4;
+    const float* src = p.partial + (size_t)sp.x * p.M * p.d;
+    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < n4; x += gridDim.x * blockDim.x) {
+        f32x4 a = *reinterpret_cast<const f32x4*>(src + (size_t)x * 4);
+        for (int i = 1; i < sp.y; ++i) a += *reinterpret_cast<const f32x4*>(src + ((size_t)i * n4 + x) * 4);
+        const int r = x / C4, col = (x - r * C4) * 4;
+        float* dst = UP ? p.out + ((size_t)e * p.H + (size_t)c * p.M + r) * p.d + col
+                        : p.out + ((size_t)e * p.d + r) * p.H + (size_t)c * p.M + col;
+        *reinterpret_cast<f32x4*>(dst) = a;
+    }
+}
 
 // Position in a 32-row group of LDS at which index i (0..31) is stored so
 // that the MFMA hands lane l the outputs 16 (l / 32) + 0..15 (wcol's inverse).
@@ -69,9 +154,12 @@ void wgrad_kernel(WgradParams p) {
     const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wq = wave / WP, wp = wave % WP;
-    const int slab = blockIdx.x / p.ntn, tn = blockIdx.x - slab * p.ntn;
+    const int un = blockIdx.x / p.ntn, tn = blockIdx.x - un * p.ntn;
+    const int* ui = reinterpret_cast<const int*>(p.units + un);
+    const int slab = ld_uniform(ui), row0 = ld_uniform(ui + 1), cnt = ld_uniform(ui + 2), slot = ld_uniform(ui + 3);
+    if (slab < 0) return;
     const int e = slab / p.B, c = slab - e * p.B;
-    const int cnt = ld_uniform(p.slab_count + slab), so = ld_uniform(p.slab_off + slab);
+    const int so = ld_uniform(p.slab_off + slab) + row0;
     const int n0 = tn * (UP ? TP : TQ);
 
     // This thread's unit: rows 8 ro .. 8 ro + 7 of each stage, 16-byte chunk
@@ -219,8 +307,12 @@ void wgrad_kernel(WgradParams p) {
 #pragma unroll
     for (int i = 0; i < GQ; ++i) {
         const int qi = wq * GQ * 32 + i * 32 + lr;
-        float* row = UP ? p.out + ((size_t)e * p.H + (size_t)c * p.M + qi) * p.d + n0
-                        : p.out + ((size_t)e * p.d + n0 + qi) * p.H + (size_t)c * p.M;
+        float* row;
+        if (slot < 0)
+            row = UP ? p.out + ((size_t)e * p.H + (size_t)c * p.M + qi) * p.d + n0
+                     : p.out + ((size_t)e * p.d + n0 + qi) * p.H + (size_t)c * p.M;
+        else
+            row = p.partial + (size_t)slot * p.M * p.d + (UP ? (size_t)qi * p.d + n0 : (size_t)(n0 + qi) * p.M);
 #pragma unroll
         for (int j = 0; j < GP; ++j) {
             float* dst = row + wp * GP * 32 + j * 32 + 16 * lh;

@@ -1,0 +1,39 @@
+"""Weight gradients of slabs long enough to be split into units of rows (over
+24 stages of 64 rows), against the oracle by the protocol of
+tests/test_gpu_backward.py (MI355X only), and bitwise repeatable."""
+import pytest
+
+from synth import generate, get_config, layer_config, upstream_grad
+from tests.test_gpu_backward import run_backward
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+CASES = {
+    # one token past 24 stages in the shared expert's slabs (alpha = 1: every
+    # token on both blocks, the residual slabs are empty)
+    "25_stages": dict(n_tokens=24 * 64 + 1, n_blocks=2, alpha_mode="fixed", alpha_fixed=1.0),
+    # 24 stages exactly: not split
+    "24_stages": dict(n_tokens=24 * 64, n_blocks=2, alpha_mode="fixed", alpha_fixed=1.0),
+    # six parts, a ragged last one
+    "141_stages": dict(n_tokens=9001, n_blocks=2, alpha_mode="fixed", alpha_fixed=1.0),
+    # two parts in some slabs, one in others, two n tiles
+    "mixed": dict(n_tokens=5000, n_blocks=3, d_model=256, block_width=128),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_split_slabs(name):
+    over = dict(dict(d_model=128, n_experts=2, block_width=64), **CASES[name])
+    g = generate(get_config("vit_s16", max_shared=over["n_blocks"], **over))
+    run_backward(g, f"units {name}")
+    from paper_2608_10392_amd.layer import DeviceLayer
+    dev = DeviceLayer(layer_config(g["cfg"]), g["X"], g["valid"], g["W_router"], g["prototypes"], g["W_up"],
+                      g["W_down"])
+    dY = upstream_grad(g)
+    a = {k: v.clone() for k, v in dev.backward(dY).items()}
+    b = dev.backward(dY)
+    torch.cuda.synchronize()
+    for k in a:
+        assert torch.equal(a[k], b[k]), f"{k} is not bitwise repeatable"
