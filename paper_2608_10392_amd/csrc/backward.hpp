@@ -8,7 +8,7 @@
 //
 // bf16 layers run on the matrix cores (the up and down engines of
 // ffn_bf16.hpp with backward epilogues, and wgrad.hpp); the kernels here are
-// the per-pair and per-token scalars (bwd_weight_kernel,
+// the per-pair and per-token scalars (bwd_weights,
 // bwd_dcoef_sum_kernel, bwd_token_kernel, the router kernels).
 // fp32 layers run on the matrix cores in fp32 (ffn_f32.hpp); the kernels here
 // serve both.
@@ -55,12 +55,14 @@ __device__ __forceinline__ float pair_weight(const BwdParams& p, int t, int e) {
     return 0.f;
 }
 
-// Pair weights: alpha for the shared expert, p_i for residual expert q_i.
-__global__ __launch_bounds__(256) void bwd_weight_kernel(BwdParams p) {
+// Pair weights: alpha for the shared expert, p_i for residual expert q_i
+// (workgroup b of n).
+__device__ __forceinline__ void bwd_weights(const BwdParams& p, int b, int n) {
     const int P = p.totals[0];
-    for (int pr = blockIdx.x * blockDim.x + threadIdx.x; pr < P; pr += gridDim.x * blockDim.x)
+    for (int pr = b * blockDim.x + threadIdx.x; pr < P; pr += n * blockDim.x)
         p.pw[pr] = pair_weight(p, p.pair_token[pr], p.pair_expert[pr]);
 }
+__global__ __launch_bounds__(256) void bwd_weight_kernel(BwdParams p) { bwd_weights(p, blockIdx.x, gridDim.x); }
 
 // dcoef[pr] = dy_{tok(pr)} . E_pr from the partial sums that the dy V pass
 // leaves per (pair, block), npb of them (bf16 layers: the two column halves;
@@ -278,13 +280,28 @@ __global__ __launch_bounds__(64) void bwd_router_kernel(BwdParams p) {
         }
 }
 
+// The slices' sum: four threads per element take 64 slices each (8 loads in
+// flight), and their four sums are added in order (one thread per element took
+// 12.7 us whatever the layer).
 __global__ __launch_bounds__(256) void bwd_router_sum_kernel(BwdParams p) {
-    const size_t item = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ float part[4][64];
     const size_t n = (size_t)(p.K + 1) * p.d;
-    if (item >= n) return;
+    const int lane = lane_id(), g = (int)threadIdx.x >> 6;
+    const size_t item = (size_t)blockIdx.x * 64 + lane;
     float s = 0.f;
-    for (int c = 0; c < kRouterChunks; ++c) s += p.rpart[(size_t)c * n + item];
-    p.dWr[item] = s;
+    if (item < n) {
+        const float* src = p.rpart + (size_t)g * (kRouterChunks / 4) * n + item;
+        for (int c = 0; c < kRouterChunks / 4; c += 8) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = src[(size_t)(c + u) * n];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += v[u];
+        }
+    }
+    part[g][lane] = s;
+    __syncthreads();
+    if (g == 0 && item < n) p.dWr[item] = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
 }
 
 // Gram diversity loss of the augmented router (Eq. diversity-loss):
@@ -296,7 +313,6 @@ struct DivParams {
     int K1, d;
     const float* W;      // [K+1, d]
     double* G;           // [K+1, K+1] workspace
-    double* Ls;          // [1] workspace: L_div
     float* loss;         // [1]
     float* dW;           // [K+1, d], updated
     float lambda;
@@ -325,10 +341,9 @@ __global__ __launch_bounds__(256) void div_gram_kernel(DivParams p) {
     }
 }
 
-// L_div from G (one workgroup of 256: strided partial sums, then a fixed
-// tree in LDS).
-__global__ __launch_bounds__(256) void div_loss_kernel(DivParams p) {
-    __shared__ double part[256];
+// L_div from G by one workgroup of 256 (strided partial sums, then a fixed
+// tree in LDS): the same value in every workgroup that forms it.
+__device__ __forceinline__ double div_loss(const DivParams& p, double* part) {
     const int n = p.K1 * p.K1;
     double s = 0.0;
     for (int x = threadIdx.x; x < n; x += 256) {
@@ -341,18 +356,18 @@ __global__ __launch_bounds__(256) void div_loss_kernel(DivParams p) {
         if ((int)threadIdx.x < h) part[threadIdx.x] += part[threadIdx.x + h];
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        const double L = sqrt(part[0]);
-        *p.Ls = L;
-        *p.loss = (float)L;
-    }
+    return sqrt(part[0]);
 }
 
-// dW[i][n] += lambda (2 / L) sum_j (G - I)[i][j] W[j][n], one thread per (i, n).
+// dW[i][n] += lambda (2 / L) sum_j (G - I)[i][j] W[j][n], one thread per (i, n);
+// every workgroup forms L itself (a launch of its own took longer), the first
+// writes it.
 __global__ __launch_bounds__(256) void div_grad_kernel(DivParams p) {
+    __shared__ double part[256];
+    const double L = div_loss(p, part);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *p.loss = (float)L;
     const size_t item = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (item >= (size_t)p.K1 * p.d) return;
-    const double L = *p.Ls;
     if (L == 0.0 || p.lambda == 0.0f) return;
     const int i = (int)(item / p.d), n = (int)(item - (size_t)i * p.d);
     double g = 0.0;

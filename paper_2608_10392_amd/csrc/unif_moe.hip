@@ -311,7 +311,7 @@ FwdPlan plan_forward(const Dims& m, size_t xn_bytes = 0) {
     p.exp_total = cv.take(4 * (size_t)kExpCopies * K1);
     p.totals = cv.take(4 * 8);
     p.down_slices = cv.take(4 * (kXcds + 1));
-    p.queues = cv.take(4 * 16);   // per-XCD tile counters: up, then down
+    p.queues = cv.take(4 * 64);   // per-XCD tile counters: up, down, then the backward's three passes
     p.zero_page = cv.take(256);
     p.zero_end = cv.cur;
     p.work = cv.take(16);   // unif_moe_forward_work's counter
@@ -780,7 +780,9 @@ int32_t forward_impl(const unif_moe_config* cfg, const unif_moe_block* blk, cons
         UNIF_LAUNCH_CHECK();
     }
     if (m.bf16) {
-        // The down tiles of each XCD's queue, split by cost.
+        // The down tiles of each XCD's queue, split by cost. (As the tail of
+        // the tables' launch, by its last workgroup, this was slower: every
+        // workgroup then has to write its L2 back, 40 us on vit_b16.)
         down_slices_kernel<<<1, kSliceThreads, 0, st>>>(pp);
         UNIF_LAUNCH_CHECK();
         UNIF_MARK(3);
@@ -1005,7 +1007,7 @@ namespace {
 // layers), for bf16 layers V^T, the per-(pair, block) partial sums of dy . E
 // and the per-pair and per-token scalars.
 struct BwdPlan {
-    size_t fwd, da, gbuf, wdnT, dcp, dcoef, pw, dz, rpart, queues, units, split, total;
+    size_t fwd, da, gbuf, wdnT, dcp, dcoef, pw, dz, rpart, units, split, total;
     int extra;   // units of the weight gradients on top of one per slab, at most
     int slots;   // partial sums of split weight-gradient slabs that fit the per-pair rows' region
 };
@@ -1024,16 +1026,18 @@ BwdPlan plan_backward(const Dims& m) {
     b.pw = cv.take(pmax * sizeof(float));
     b.dz = cv.take((size_t)m.N * m.K1 * sizeof(float));
     b.rpart = cv.take((size_t)kRouterChunks * m.K1 * m.d * sizeof(float));
-    b.queues = cv.take(4 * 32);
     // The weight gradients' units; their partial sums take the place of the
     // per-pair rows, which are done with by then.
     b.slots = m.bf16 ? (int)std::min<size_t>(pmax / (2 * m.M), (size_t)1 << 16) : 0;   // for each of the two gradients
-    b.extra = m.bf16 ? ceil_div(512, m.d % 256 == 0 ? m.d / 256 : m.d / 128) : 0;   // 512 tiles: two per compute unit
+    b.extra = m.bf16 ? ceil_div(512, wgrad_ntn(m)) : 0;   // 512 tiles: two per compute unit
     b.units = cv.take(m.bf16 ? 16 * ((size_t)m.nslab + b.extra) : 0);
     b.split = cv.take(m.bf16 ? 8 * (size_t)m.nslab : 0);
     b.total = cv.cur + 256;
     return b;
 }
+// n tiles of a slab's weight gradients (256 columns each, else 128).
+int wgrad_ntn(const Dims& m) { return m.d % 256 == 0 ? m.d / 256 : m.d / 128; }
+
 
 constexpr int kF32BackwardMaxTokens = 8388480;   // the documented bound
 
@@ -1155,8 +1159,6 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
         }
         return UNIF_OK;
     }
-    bwd_weight_kernel<<<(unsigned)cus * 4, 256, 0, st>>>(p);
-    UNIF_LAUNCH_CHECK();
     const size_t pmax = (size_t)m.N * m.K1;
     u16* const abuf = reinterpret_cast<u16*>(ws + fp.hbuf);
     u16* const gbuf = reinterpret_cast<u16*>(ws + bp.gbuf);
@@ -1165,16 +1167,22 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
     if (m.bf16) {
         // 2. V^T [K+1, H, d] (rows of dy V as the up kernel's weights) and
         //    K^T [K+1, d, H] (dx_pair = da K as the down kernel's weights)
-        int* queues = reinterpret_cast<int*>(ws + bp.queues);
-        fill_zero_kernel<<<1, 64, 0, st>>>(reinterpret_cast<uint32_t*>(queues), 32);
-        UNIF_LAUNCH_CHECK();
+        //    with the pair weights and the weight gradients' units
+        int* const queues = reinterpret_cast<int*>(ws + fp.queues) + 16;   // zeroed with the forward's counters
         u16* const wdnT = reinterpret_cast<u16*>(ws + bp.wdnT);
         u16* const wupT = reinterpret_cast<u16*>(ws + fp.wdown16);
-        const int nt = m.K1 * (m.d / 64) * (m.H / 64);
-        transpose16_kernel<<<(unsigned)ceil_div(nt, 4), 256, 0, st>>>(static_cast<const u16*>(W_down), wdnT, m.d,
-                                                                       m.H, nt);
-        transpose16_kernel<<<(unsigned)ceil_div(nt, 4), 256, 0, st>>>(static_cast<const u16*>(W_up), wupT, m.H,
-                                                                       m.d, nt);
+        WgradUnitParams wu;
+        wu.nslab = m.nslab;
+        wu.ntn = wgrad_ntn(m);
+        wu.cus = cus;
+        wu.slots = bp.slots;
+        wu.extra = bp.extra;
+        wu.slab_count = reinterpret_cast<const int*>(ws + fp.slab_count);
+        wu.units = reinterpret_cast<int4*>(ws + bp.units);
+        wu.split = reinterpret_cast<int2*>(ws + bp.split);
+        const int nt = m.K1 * (m.d / 64) * (m.H / 64), nw = cus;
+        bwd_prepare_kernel<<<(unsigned)(1 + nw + 2 * ceil_div(nt, 4)), 256, 0, st>>>(
+            p, wu, nw, static_cast<const u16*>(W_down), wdnT, static_cast<const u16*>(W_up), wupT, nt);
         UNIF_LAUNCH_CHECK();
         // 3. a = x K^T over the slabs (kept in fp16); then dy V: the dy . E
         //    partials, da and w GELU(a)
@@ -1231,6 +1239,8 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
         dn.split_stride = 0;
         if (dsh.bn == 384)
             s = launch_persistent(down_kernel<2, 3, false>, grid, (size_t)down_lds_bytes(128, 384), st, dn);
+        // (Summed inside bwd_token_kernel instead, whose few waves wait for
+        // every load, this was 38 us slower on DeiT-S.)
         else if (dsh.bn == 256)
             s = launch_persistent(down_kernel<4, 4, false>, grid, (size_t)down_lds_bytes(256, 256), st, dn);
         else
@@ -1256,7 +1266,7 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
     if (m.bf16) bwd_router_kernel<true><<<rgrid, 64, 0, st>>>(p);
     else bwd_router_kernel<false><<<rgrid, 64, 0, st>>>(p);
     UNIF_LAUNCH_CHECK();
-    bwd_router_sum_kernel<<<(unsigned)ceil_div(m.K1 * m.d, 256), 256, 0, st>>>(p);
+    bwd_router_sum_kernel<<<(unsigned)ceil_div(m.K1 * m.d, 64), 256, 0, st>>>(p);
     UNIF_LAUNCH_CHECK();
     // 6. expert weight gradients
     if (m.bf16) {
@@ -1265,23 +1275,14 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
         w.M = m.M;
         w.B = m.B;
         w.H = m.H;
-        w.ntn = (m.d % 256 == 0) ? m.d / 256 : m.d / 128;
+        w.ntn = wgrad_ntn(m);
         w.slab_rows = reinterpret_cast<const int*>(ws + fp.slab_rows);
+        bwd_weight_kernel<<<(unsigned)cus * 4, 256, 0, st>>>(p);
         w.slab_tok = reinterpret_cast<const int*>(ws + fp.slab_tok);
         w.slab_off = reinterpret_cast<const int*>(ws + fp.slab_off);
         w.slab_count = reinterpret_cast<const int*>(ws + fp.slab_count);
-        WgradUnitParams wu;
-        wu.nslab = m.nslab;
-        wu.ntn = w.ntn;
-        wu.cus = cus;
-        wu.slots = bp.slots;
-        wu.extra = bp.extra;
-        wu.slab_count = w.slab_count;
-        wu.units = reinterpret_cast<int4*>(ws + bp.units);
-        wu.split = reinterpret_cast<int2*>(ws + bp.split);
-        wgrad_units_kernel<<<1, kWgradUnitThreads, 0, st>>>(wu);
-        UNIF_LAUNCH_CHECK();
-        w.units = wu.units;
+        w.units = reinterpret_cast<const int4*>(ws + bp.units);
+        const int2* const split = reinterpret_cast<const int2*>(ws + bp.split);
         w.partial = p.dxp;
         w.Psrc = static_cast<const u16*>(X);
         w.Qsrc = gbuf;
@@ -1297,7 +1298,7 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
         if (s != UNIF_OK) return s;
         if (bp.slots > 0) {
             const dim3 sgrid((unsigned)std::min(ceil_div(m.M * m.d / 4, 256), 16), (unsigned)m.nslab, 2);
-            wgrad_sum_kernel<<<sgrid, 256, 0, st>>>(w_up, w, wu.split);
+            wgrad_sum_kernel<<<sgrid, 256, 0, st>>>(w_up, w, split);
             UNIF_LAUNCH_CHECK();
         }
     } else {
@@ -1336,14 +1337,11 @@ int32_t unif_moe_diversity_loss(const unif_moe_config* cfg, const float* W_route
     dp.W = W_router;
     char* ws = align_base(workspace);
     dp.G = reinterpret_cast<double*>(ws);
-    dp.Ls = dp.G + (size_t)dp.K1 * dp.K1;
     dp.loss = loss;
     dp.dW = dW_router;
     dp.lambda = lambda;
     const int npair = dp.K1 * (dp.K1 + 1) / 2;
     div_gram_kernel<<<(unsigned)ceil_div(npair, 4), 256, 0, st>>>(dp);
-    UNIF_LAUNCH_CHECK();
-    div_loss_kernel<<<1, 256, 0, st>>>(dp);
     UNIF_LAUNCH_CHECK();
     div_grad_kernel<<<(unsigned)ceil_div(dp.K1 * dp.d, 256), 256, 0, st>>>(dp);
     UNIF_LAUNCH_CHECK();

@@ -19,7 +19,7 @@
 //
 // The shared expert's slabs are several times longer than the residual ones
 // (DeiT-S, 18,912 tokens: 148 stages against 50, and 168 tiles in all), so
-// long slabs are split by rows into units (wgrad_units_kernel), whose partial
+// long slabs are split by rows into units (wgrad_units), whose partial
 // sums are added in row order by wgrad_sum_kernel. One workgroup per unit and
 // n tile. (Persistent workgroups taking the tiles from a queue, and per-XCD
 // runs of them in token order, were slower: 56 -> 70 us per gradient on the
@@ -32,6 +32,7 @@
 #pragma once
 #include "common.hpp"
 #include "ffn_bf16.hpp"
+#include "backward.hpp"
 #include "permute.hpp"
 
 namespace unifmoe {
@@ -60,7 +61,7 @@ struct WgradParams {
 // 328 -> 173 us with the sums); vit_b16 (394 stages against an even share of 323) and
 // the padded BERT-base batch split none.
 constexpr int kWgradMinStages = 24;
-constexpr int kWgradUnitThreads = 1024;
+constexpr int kWgradUnitThreads = 256;
 struct WgradUnitParams {
     int nslab, ntn, cus, slots, extra;
     const int* slab_count;
@@ -68,7 +69,7 @@ struct WgradUnitParams {
     int2* split;              // [nslab]: first partial slot, parts (1: none)
 };
 
-__global__ __launch_bounds__(kWgradUnitThreads) void wgrad_units_kernel(WgradUnitParams p) {
+__device__ __forceinline__ void wgrad_units(const WgradUnitParams& p) {
     __shared__ int lds[kWgradUnitThreads / 64];
     const int tid = threadIdx.x, T = blockDim.x;
     const int per = ceil_div(p.nslab, T), s0 = min(p.nslab, tid * per), s1 = min(p.nslab, s0 + per);
@@ -330,9 +331,8 @@ void wgrad_kernel(WgradParams p) {
 // lane / 8) loads rows 8 ro .. 8 ro + 7 of 16-byte chunk ch and stores the
 // transposed 8 x 8 block as 8 rows of 8 (each store instruction writes 8
 // whole 128-byte rows).
-__global__ __launch_bounds__(256) void transpose16_kernel(const u16* __restrict__ in, u16* __restrict__ out, int R,
-                                                           int C, int ntiles) {
-    const int t = blockIdx.x * 4 + (int)(threadIdx.x >> 6);
+__device__ __forceinline__ void transpose16(const u16* __restrict__ in, u16* __restrict__ out, int R, int C, int t,
+                                            int ntiles) {
     if (t >= ntiles) return;
     const int tr = R / 64, tc = C / 64;
     const int e = t / (tr * tc), rem = t - e * (tr * tc);
@@ -345,6 +345,27 @@ __global__ __launch_bounds__(256) void transpose16_kernel(const u16* __restrict_
     u16* d = out + (size_t)e * R * C + (size_t)(c0 + 8 * ch) * R + r0 + 8 * ro;
 #pragma unroll
     for (int j = 0; j < 8; ++j) st16(d + (size_t)j * R, column8(v, j));
+}
+
+// What the bf16 backward needs besides the permutation, in one launch by
+// role: the first workgroup the weight gradients' units, the next nw the pair
+// weights, then V^T and K^T (4 tiles a workgroup).
+__global__ __launch_bounds__(256) void bwd_prepare_kernel(BwdParams p, WgradUnitParams u, int nw, const u16* Wdown,
+                                                           u16* wdnT, const u16* Wup, u16* wupT, int ntiles) {
+    int b = blockIdx.x;
+    if (b == 0) {
+        wgrad_units(u);
+        return;
+    }
+    b -= 1;
+    if (b < nw) {
+        bwd_weights(p, b, nw);
+        return;
+    }
+    b -= nw;
+    const int nt = ceil_div(ntiles, 4), t = (b % nt) * 4 + (int)(threadIdx.x >> 6);
+    if (b < nt) transpose16(Wdown, wdnT, p.d, p.H, t, ntiles);
+    else transpose16(Wup, wupT, p.H, p.d, t, ntiles);
 }
 
 }  // namespace unifmoe

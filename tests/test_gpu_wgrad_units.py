@@ -10,15 +10,17 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
+# b = 1 of 2 blocks, block 0 by prefix: every token is on slab (0, 0), and its
+# residual expert's pair on block 1. (A few tokens near a tie are left out.)
+PREFIX = dict(n_blocks=2, alpha_mode="fixed", alpha_fixed=0.5, select_mode="prefix")
 CASES = {
-    # one token past 24 stages in the shared expert's slabs (alpha = 1: every
-    # token on both blocks, the residual slabs are empty)
-    "25_stages": dict(n_tokens=24 * 64 + 1, n_blocks=2, alpha_mode="fixed", alpha_fixed=1.0),
-    # 24 stages exactly: not split
-    "24_stages": dict(n_tokens=24 * 64, n_blocks=2, alpha_mode="fixed", alpha_fixed=1.0),
+    # just past 24 stages: two parts
+    "25_stages": dict(n_tokens=24 * 64 + 20, **PREFIX),
+    # 24 stages: not split
+    "24_stages": dict(n_tokens=24 * 64, **PREFIX),
     # six parts, a ragged last one
-    "141_stages": dict(n_tokens=9001, n_blocks=2, alpha_mode="fixed", alpha_fixed=1.0),
-    # two parts in some slabs, one in others, two n tiles
+    "141_stages": dict(n_tokens=9001, **PREFIX),
+    # two parts in some slabs, one in others, wider tiles
     "mixed": dict(n_tokens=5000, n_blocks=3, d_model=256, block_width=128),
 }
 
