@@ -901,22 +901,25 @@ int32_t forward_impl(const unif_moe_config* cfg, const unif_moe_block* blk, cons
         bc.Y = Y;
         bc.totals = totals;
         if (!bc.post) {
-            const int nch = m.bf16 ? m.d / 8 : m.d;
+            const int nch = m.bf16 ? m.d / 4 : m.d;
             const unsigned g = (unsigned)(((size_t)m.N * nch + 255) / 256);
             if (m.bf16) combine_block_flat_kernel<true><<<g, 256, 0, st>>>(bc);
             else combine_block_flat_kernel<false><<<g, 256, 0, st>>>(bc);
         } else {
-            // One fp32 row per wave in LDS: 4 rows per workgroup while that
-            // fits in 64 KB, else one.
-            const int rows = ((size_t)16 * m.d <= 65536) ? 4 : 1;
-            const size_t lds = (size_t)rows * m.d * sizeof(float);
-            const unsigned g = (unsigned)ceil_div(m.N, rows);
+            // One fp32 row in LDS; one chunk per thread up to 256 threads.
+            // Rows that fill LDS leave no room for the waves' sums: one wave.
+            unsigned threads = (unsigned)std::min(256, ceil_div(m.bf16 ? m.d / 8 : m.d, 64) * 64);
+            size_t lds = (size_t)((m.d + 1) & ~1) * sizeof(float) + (threads / 64) * sizeof(double);
+            if (lds > kLdsLimit) {
+                threads = 64;
+                lds = (size_t)m.d * sizeof(float);
+            }
             if (m.bf16) {
                 if (allow_lds(combine_block_post_kernel<true>, lds) != UNIF_OK) return UNIF_EDEVICE;
-                combine_block_post_kernel<true><<<g, 64 * rows, lds, st>>>(bc);
+                combine_block_post_kernel<true><<<(unsigned)m.N, threads, lds, st>>>(bc);
             } else {
                 if (allow_lds(combine_block_post_kernel<false>, lds) != UNIF_OK) return UNIF_EDEVICE;
-                combine_block_post_kernel<false><<<g, 64 * rows, lds, st>>>(bc);
+                combine_block_post_kernel<false><<<(unsigned)m.N, threads, lds, st>>>(bc);
             }
         }
         UNIF_LAUNCH_CHECK();
