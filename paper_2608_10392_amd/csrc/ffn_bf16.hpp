@@ -209,7 +209,7 @@ void up_kernel(UpParams p) {
     constexpr int RB = S::RB, KS = S::KSTEPS, NWV = kFfnWaves;
     constexpr int M = MG * 64;                        // MG 32-column groups per wave
     constexpr int RG = TM / 128;                      // 32-row groups per wave (4 row waves)
-    static_assert(TM == 256 || TM == 384, "tile heights with whole row-list copies");
+    static_assert(TM == 128 || TM == 256 || TM == 384, "tile heights with whole row-list copies");
     constexpr int LA = TM / S::ROWS_PER_DMA / NWV;    // token-row copies per wave per stage
     constexpr int LB = M / S::ROWS_PER_DMA / NWV;     // weight-row copies per wave per stage
     constexpr int L = LA + LB;
@@ -220,11 +220,11 @@ void up_kernel(UpParams p) {
     constexpr int NEPI = RG * MG * (EPI == kEpiDa ? 4 : 2);
     constexpr int A_BYTES = TM * RB, STAGE = (TM + M) * RB, RING = 2 * STAGE;
     // 4-byte copies per wave for a tile's row lists (2 TM ints): one of 64
-    // ints per wave, and for TM = 384 one more of 32.
+    // ints per wave (TM = 128: of 32), and for TM = 384 one more of 32.
     constexpr int NFETCH = (2 * TM > NWV * 64) ? 2 : 1;
     constexpr int NR = RG + MG;                       // fragment reads per k step
     static_assert(LA >= 1 && LB >= 1, "tile too small for one copy per wave");
-    static_assert(2 * TM == NWV * 64 || 2 * TM == NWV * 96, "row lists: one or one and a half copies per wave");
+    static_assert(2 * TM % (NWV * 32) == 0 && 2 * TM <= NWV * 96, "row lists: at most one and a half copies per wave");
     static_assert(NEPI + NFETCH + L < 64, "vmcnt range");
     extern __shared__ __attribute__((aligned(16))) char lds_up[];
     // rows[par][0] tokens, rows[par][1] pairs of the tile with parity par
@@ -276,8 +276,10 @@ void up_kernel(UpParams p) {
     // the same number of operations.
     auto fetch_rows = [&](int first, int par) {
         int* dst = rows + par * 2 * TM;
-        const int i0 = wave * 64;   // the list boundary TM is a multiple of 64
-        dma4((i0 < TM ? p.slab_tok + first + i0 : p.slab_rows + first + (i0 - TM)) + lane, dst + i0);
+        constexpr int W = TM == 128 ? 32 : 64;
+        const int i0 = wave * W;   // the list boundary TM is a multiple of W
+        if (W == 64 || lane < W)
+            dma4((i0 < TM ? p.slab_tok + first + i0 : p.slab_rows + first + (i0 - TM)) + lane, dst + i0);
         if constexpr (NFETCH == 2) {
             const int i1 = NWV * 64 + wave * 32;
             if (lane < 32) dma4(p.slab_rows + first + (i1 - TM) + lane, dst + i1);

@@ -61,8 +61,17 @@ constexpr int kSplitKTiles = 256;
 // gathered rows x the whole block width M. Down: see down_shape.
 // Up tiles are 384 rows when the block is at most 192 wide and no stage is
 // padding (d >= 256): their accumulators and fragments then still fit two
-// waves per SIMD without spills. Else 256.
-int up_tm(int M, int d) { return (M <= 192 && d >= 256) ? 384 : 256; }
+// waves per SIMD without spills. Else 256. Small calls, whose slabs are
+// estimated (4 pairs per token, half of the blocks each) to fill no more than
+// one such tile, take 128: the rows a slab lacks cost a tile as much as those
+// it has, in products and above all in the GELU of the epilogue (one image of
+// a DeiT-S layer, 56 rows a slab: 20.8 -> 11.3 us).
+constexpr int kUpSmallRows = 384;
+int up_tm(int N, int K1, int M, int d) {
+    if (d < 256) return 256;
+    if ((int64_t)N * std::min(K1, 4) <= (int64_t)2 * kUpSmallRows * K1) return 128;
+    return M <= 192 ? 384 : 256;
+}
 // Up tiles are ordered by expert, then by groups of blocks, then by the
 // stretch of the expert's pairs they cover: the tiles that run together on
 // one XCD share token rows (across the group's blocks) and weight slabs
@@ -132,7 +141,7 @@ Dims dims_of(const unif_moe_config* c) {
 }
 
 // Rows of an up tile and of a down row tile.
-int up_rows(const Dims& m) { return m.bf16 ? up_tm(m.M, m.d) : kF32T; }
+int up_rows(const Dims& m) { return m.bf16 ? up_tm(m.N, m.K1, m.M, m.d) : kF32T; }
 int down_rows(const Dims& m) { return m.bf16 ? down_shape(m.d).tm : kF32T; }
 
 // cfg without a pair capacity (workspaces sized for the worst case).
@@ -278,7 +287,7 @@ size_t ceil_div_sz(size_t a, size_t b) { return (a + b - 1) / b; }
 // are added by the merge in order). The down kernel runs each tile's blocks
 // one after another, so when a workload has no more tiles than a 256-CU
 // device has compute units, the chip idles while those chains run: such
-// workloads get enough parts for about two tiles per compute unit. The tile
+// workloads get parts for up to two tiles per compute unit. The tile
 // count is estimated from N with 4 pairs per token (a function of cfg only,
 // since it sizes the workspace).
 int down_splits(const Dims& m) {
@@ -286,7 +295,7 @@ int down_splits(const Dims& m) {
     const DownShape dsh = down_shape(m.d);
     const size_t est_pairs = (size_t)m.N * (size_t)std::min(m.K1, 4);
     const size_t tiles = std::max<size_t>(1, ceil_div_sz(est_pairs, dsh.tm) * (size_t)(m.d / dsh.bn));
-    return tiles > 256 ? 1 : (int)std::min<size_t>(4, ceil_div_sz(2 * 256, tiles));
+    return tiles > 256 ? 1 : (int)std::min<size_t>(4, 2 * 256 / tiles);
 }
 
 // The routing record's region is reserved whether or not the caller passes
@@ -571,23 +580,21 @@ int32_t record_event(void* const* events, int i, hipStream_t st) {
         if (record_event(events, (i), st) != UNIF_OK) return UNIF_EDEVICE; \
     } while (0)
 
+template <int MG, int EPI>
+int32_t launch_up_m(const Dims& m, int grid, size_t lds, hipStream_t st, const UpParams& up) {
+    if (m.d < 256) return launch_persistent(up_kernel<MG, true, 256, EPI>, grid, lds, st, up);
+    if (up_rows(m) == 128) return launch_persistent(up_kernel<MG, false, 128, EPI>, grid, lds, st, up);
+    return launch_persistent(up_kernel<MG, false, MG <= 3 ? 384 : 256, EPI>, grid, lds, st, up);
+}
+
 // Up-projection launch for the layer's block width, with epilogue EPI.
 template <int EPI>
 int32_t launch_up(const Dims& m, int grid, size_t lds, hipStream_t st, const UpParams& up) {
-    const bool pad = m.d < 256;
     switch (m.M / 64) {
-        case 1:
-            return pad ? launch_persistent(up_kernel<1, true, 256, EPI>, grid, lds, st, up)
-                       : launch_persistent(up_kernel<1, false, 384, EPI>, grid, lds, st, up);
-        case 2:
-            return pad ? launch_persistent(up_kernel<2, true, 256, EPI>, grid, lds, st, up)
-                       : launch_persistent(up_kernel<2, false, 384, EPI>, grid, lds, st, up);
-        case 3:
-            return pad ? launch_persistent(up_kernel<3, true, 256, EPI>, grid, lds, st, up)
-                       : launch_persistent(up_kernel<3, false, 384, EPI>, grid, lds, st, up);
-        case 4:
-            return pad ? launch_persistent(up_kernel<4, true, 256, EPI>, grid, lds, st, up)
-                       : launch_persistent(up_kernel<4, false, 256, EPI>, grid, lds, st, up);
+        case 1: return launch_up_m<1, EPI>(m, grid, lds, st, up);
+        case 2: return launch_up_m<2, EPI>(m, grid, lds, st, up);
+        case 3: return launch_up_m<3, EPI>(m, grid, lds, st, up);
+        case 4: return launch_up_m<4, EPI>(m, grid, lds, st, up);
         default: return UNIF_EUNSUPPORTED;
     }
 }
@@ -808,7 +815,7 @@ int32_t forward_impl(const unif_moe_config* cfg, const unif_moe_block* blk, cons
         up.totals = totals;
         up.queue = reinterpret_cast<int*>(ws + plan.queues);
         up.b_up = blk != nullptr ? blk->b_up : nullptr;
-        const size_t up_lds = (size_t)up_lds_bytes(m.M, up_tm(m.M, m.d));
+        const size_t up_lds = (size_t)up_lds_bytes(m.M, up_rows(m));
         const int grid = (cus / kXcds) * kXcds;
         s = up.b_up != nullptr ? launch_up<kEpiGeluBias>(m, grid, up_lds, st, up)
                                 : launch_up<kEpiGelu>(m, grid, up_lds, st, up);
@@ -1015,6 +1022,9 @@ struct BwdPlan {
     int slots;   // partial sums of split weight-gradient slabs that fit the per-pair rows' region
 };
 
+// n tiles of a slab's weight gradients (256 columns each, else 128).
+int wgrad_ntn(const Dims& m) { return m.d % 256 == 0 ? m.d / 256 : m.d / 128; }
+
 BwdPlan plan_backward(const Dims& m) {
     BwdPlan b;
     b.fwd = plan_forward(m).total;   // includes its own 256 bytes of alignment slack
@@ -1038,9 +1048,6 @@ BwdPlan plan_backward(const Dims& m) {
     b.total = cv.cur + 256;
     return b;
 }
-// n tiles of a slab's weight gradients (256 columns each, else 128).
-int wgrad_ntn(const Dims& m) { return m.d % 256 == 0 ? m.d / 256 : m.d / 128; }
-
 
 constexpr int kF32BackwardMaxTokens = 8388480;   // the documented bound
 
@@ -1209,7 +1216,7 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
         up.pw = p.pw;
         up.dcp = dcp;
         up.sink_row = (int)pmax;
-        const size_t up_lds = (size_t)up_lds_bytes(m.M, up_tm(m.M, m.d));
+        const size_t up_lds = (size_t)up_lds_bytes(m.M, up_rows(m));
         const int grid = (cus / kXcds) * kXcds;
         s = launch_up<kEpiPre>(m, grid, up_lds, st, up);
         if (s != UNIF_OK) return s;
@@ -1218,6 +1225,8 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
         up.queue = queues + 8;
         s = launch_up<kEpiDa>(m, grid, up_lds, st, up);
         if (s != UNIF_OK) return s;
+        // (Summed inside bwd_token_kernel instead, whose few waves wait for
+        // every load, this was 38 us slower on DeiT-S.)
         bwd_dcoef_sum_kernel<<<(unsigned)cus * 4, 256, 0, st>>>(p, dcp, 2);
         UNIF_LAUNCH_CHECK();
         // 4. dx_pair = da K over each pair's blocks
@@ -1242,8 +1251,6 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
         dn.split_stride = 0;
         if (dsh.bn == 384)
             s = launch_persistent(down_kernel<2, 3, false>, grid, (size_t)down_lds_bytes(128, 384), st, dn);
-        // (Summed inside bwd_token_kernel instead, whose few waves wait for
-        // every load, this was 38 us slower on DeiT-S.)
         else if (dsh.bn == 256)
             s = launch_persistent(down_kernel<4, 4, false>, grid, (size_t)down_lds_bytes(256, 256), st, dn);
         else
@@ -1256,6 +1263,7 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
         f.da = reinterpret_cast<float*>(ws + bp.da);
         f.dcp = dcp;
         f.pw = p.pw;
+        bwd_weight_kernel<<<(unsigned)cus * 4, 256, 0, st>>>(p);
         f32_up_kernel<kF32Pre><<<f32_grid(cus), 256, 0, st>>>(f);
         f32_up_kernel<kF32Da><<<f32_grid(cus), 256, 0, st>>>(f);
         bwd_dcoef_sum_kernel<<<(unsigned)cus * 4, 256, 0, st>>>(p, dcp, 2 * f32_chunks(m.M));
@@ -1280,7 +1288,6 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
         w.H = m.H;
         w.ntn = wgrad_ntn(m);
         w.slab_rows = reinterpret_cast<const int*>(ws + fp.slab_rows);
-        bwd_weight_kernel<<<(unsigned)cus * 4, 256, 0, st>>>(p);
         w.slab_tok = reinterpret_cast<const int*>(ws + fp.slab_tok);
         w.slab_off = reinterpret_cast<const int*>(ws + fp.slab_off);
         w.slab_count = reinterpret_cast<const int*>(ws + fp.slab_count);
@@ -1524,7 +1531,7 @@ int32_t unif_moe_forward_work(const unif_moe_config* cfg, const void* workspace,
     host_out->pairs = t[0];
     host_out->up_tiles = t[1];
     host_out->down_tiles = t[2];
-    host_out->up_mfma_flops = (double)t[1] * up_tm(m.M, m.d) * dM * dd * 2.0;
+    host_out->up_mfma_flops = (double)t[1] * up_rows(m) * dM * dd * 2.0;
     host_out->down_mfma_flops = (double)g * 32.0 * dM * dd * 2.0;
     host_out->down_parts = down_splits(m);
     for (int x = 0; x < kXcds; ++x) host_out->down_queued += std::max(0, sl[x + 1] - sl[x]);
