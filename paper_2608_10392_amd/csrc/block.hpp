@@ -25,9 +25,12 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
 // to 8 significant bits equals rounding the fp64 value directly (the fp32
 // format has at least two more bits), in the normal range.
 __device__ __forceinline__ u16 f64_to_bf16(double v) {
-    float f = __double2float_rz(v);
-    if ((double)f != v) f = __uint_as_float(__float_as_uint(f) | 1u);
-    return f2bf(f);
+    const float f = (float)v;
+    const double d = (double)f;
+    uint32_t u = __float_as_uint(f);
+    // f rounded away from zero: one step back, then the sticky bit.
+    if (d != v) u = (u - (fabs(d) > fabs(v) ? 1u : 0u)) | 1u;
+    return f2bf(__uint_as_float(u));
 }
 
 struct LayerNormParams {
