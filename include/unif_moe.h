@@ -184,8 +184,8 @@ int32_t unif_moe_layer_forward_workspace_size(const unif_moe_config* cfg, size_t
  *   routing_out  optional record (NULL: kept inside the workspace)
  * Precision of the bf16 path: the up-projection multiplies bf16 values
  * (exact products, fp32 accumulation); the GELU activations are rounded to
- * fp16 and multiplied with an fp16 copy of W_down (made in the workspace at
- * each call; exact for bf16 magnitudes in [2^-17, 65504], larger ones become
+ * fp16 and multiplied with W_down in fp16 (a copy made in the workspace at
+ * each call, or converted as it is read; exact for bf16 magnitudes in [2^-17, 65504], larger ones become
  * infinities), accumulating in fp32; the per-expert outputs E_j(x) stay fp32
  * and Y is rounded once to bf16. Activations beyond 65504 in magnitude are
  * not representable in fp16 and make the output infinite. The merge sums in

@@ -98,7 +98,7 @@ struct DownParams {
     int d, M, B, H, ncol;        // ncol: column tiles per row tile
     const u16* Hbuf;             // fp16 (F16 kernels) or bf16
     const u16* zero16;           // 16 zero bytes: the source of rows that lack a block
-    const u16* Wdown;            // values V in Hbuf's format, layout of the layer's W_down
+    const u16* Wdown;            // values V in Hbuf's format (CVT: bf16), layout of the layer's W_down
     float* part;                 // per-pair output rows, fp32
     float* part_sink;            // one d row that absorbs the stores of unused tile rows
     const int4* rt_info;         // per row tile: first pair, rows, expert
@@ -534,7 +534,10 @@ void up_kernel(UpParams p) {
 // lacks the stage's block reads the zero page, and a 32-row MFMA group whose
 // rows all lack it skips its MFMAs. Tiles are padded to at least 4 stages
 // with empty stages (no MFMAs).
-template <int WM, int NG, bool F16 = true>
+// CVT: the weights are the layer's bf16 W_down, converted to fp16 as their
+// fragments are used (the same rounding as the copy); else Wdown already holds
+// Hbuf's format.
+template <int WM, int NG, bool F16 = true, bool CVT = false>
 __global__ __launch_bounds__(kFfnThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void down_kernel(DownParams p) {
     using S = Stage;
@@ -750,6 +753,16 @@ void down_kernel(DownParams p) {
 #pragma unroll
                 for (int r = 0; r < NR; ++r) read_one(rslot, rk, r, X2, W2);
                 __builtin_amdgcn_sched_barrier(0);
+                if constexpr (CVT) {
+                    if (gset) {
+#pragma unroll
+                        for (int j = 0; j < NG; ++j)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q)
+                                W[j][q] = pack_f16x2(__uint_as_float(W[j][q] << 16),
+                                                     __uint_as_float(W[j][q] & 0xffff0000u));
+                    }
+                }
 #pragma unroll
                 for (int i = 0; i < RG; ++i) {
                     if (gset & (1u << i)) {

@@ -298,6 +298,16 @@ int down_splits(const Dims& m) {
     return tiles > 256 ? 1 : (int)std::min<size_t>(4, 2 * 256 / tiles);
 }
 
+// Whether the down-projection converts W_down to fp16 as it reads it instead of
+// taking the copy that the routing launch makes: a copy reads and writes every
+// weight once, the conversion costs vector instructions each time a row tile
+// reads one. The line lies at 256 tokens per expert (4 row tiles of 256 pairs
+// at 4 pairs per token). Padded BERT-large (241): routing 61 -> 29 us, down
+// 143 -> 167 us, the call 368 -> 353 us; padded BERT-base (455): 24 -> 22 us,
+// 60 -> 70 us, the call 160 -> 164 us.
+constexpr int kDownConvertTokens = 256;
+bool down_converts(const Dims& m) { return m.N <= kDownConvertTokens * m.K1; }
+
 // The routing record's region is reserved whether or not the caller passes
 // its own record, so every other offset is the same for both kinds of call
 // (unif_moe_forward_work reads the workspace a forward left behind).
@@ -684,7 +694,9 @@ int32_t forward_impl(const unif_moe_config* cfg, const unif_moe_block* blk, cons
     UNIF_MARK(0);
     // 0. the fp16 copy of W_down that the down-projection multiplies with:
     // made by extra workgroups of the routing decisions' launch (step 2)
-    const u16* wdown16 = (m.bf16 && !tables_only) ? reinterpret_cast<u16*>(ws + plan.wdown16) : nullptr;
+    const bool convert_on_read = m.bf16 && down_converts(m);
+    const u16* wdown16 =
+        (m.bf16 && !tables_only && !convert_on_read) ? reinterpret_cast<u16*>(ws + plan.wdown16) : nullptr;
     UNIF_MARK(1);
     // 1. the FFN input: LN(X) for a pre-LN block, else X
     const void* Xf = X;
@@ -829,7 +841,7 @@ int32_t forward_impl(const unif_moe_config* cfg, const unif_moe_block* blk, cons
         dn.ncol = pp.down_col_tiles;
         dn.zero16 = reinterpret_cast<const u16*>(ws + plan.zero_page);
         dn.Hbuf = up.Hbuf;
-        dn.Wdown = wdown16;
+        dn.Wdown = convert_on_read ? static_cast<const u16*>(W_down) : wdown16;
         dn.part = static_cast<float*>(part);
         dn.part_sink = dn.part + m.pcap * m.d;
         dn.rt_info = pp.rt_info;
@@ -840,11 +852,14 @@ int32_t forward_impl(const unif_moe_config* cfg, const unif_moe_block* blk, cons
         dn.nsplit = down_splits(m);
         dn.split_stride = (m.pcap + 1) * m.d;
         if (dsh.bn == 384)
-            s = launch_persistent(down_kernel<2, 3>, grid, (size_t)down_lds_bytes(128, 384), st, dn);
+            s = launch_persistent(convert_on_read ? down_kernel<2, 3, true, true> : down_kernel<2, 3>, grid,
+                                  (size_t)down_lds_bytes(128, 384), st, dn);
         else if (dsh.bn == 256)
-            s = launch_persistent(down_kernel<4, 4>, grid, (size_t)down_lds_bytes(256, 256), st, dn);
+            s = launch_persistent(convert_on_read ? down_kernel<4, 4, true, true> : down_kernel<4, 4>, grid,
+                                  (size_t)down_lds_bytes(256, 256), st, dn);
         else
-            s = launch_persistent(down_kernel<4, 2>, grid, (size_t)down_lds_bytes(256, 128), st, dn);
+            s = launch_persistent(convert_on_read ? down_kernel<4, 2, true, true> : down_kernel<4, 2>, grid,
+                                  (size_t)down_lds_bytes(256, 128), st, dn);
         if (s != UNIF_OK) return s;
         UNIF_MARK(5);
     } else {
