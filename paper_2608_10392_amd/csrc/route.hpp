@@ -210,6 +210,35 @@ __device__ __forceinline__ void wave_lds_order() {
     __builtin_amdgcn_wave_barrier();
 }
 
+// Lanes of the wave that add to the same counter, gathered so that one of them
+// can add for all: up to kGatherRounds times the first lane left takes those
+// with its key along (key < 0: not taking part); the rest stay alone. A key
+// that many lanes share is met in the first rounds. Without this the 64 atomics
+// of a wave on one counter queue up at the L2: with few masks over all tokens
+// (prefix selection, skewed demand, 51,328 tokens) the decisions' launch took
+// 82 us, 38 us now. Used where the masks are few (prefix selection, or at most
+// 4 key bits); elsewhere the rounds cost more than they save (2.5 us of one
+// image of a DeiT-S layer).
+constexpr int kGatherRounds = 4;
+struct Gather {
+    int lead, rank, count;   // the lane that adds, this lane's place, lanes in its group
+};
+__device__ __forceinline__ Gather gather_key(int key, bool few) {
+    Gather g{lane_id(), 0, 1};
+    if (!few) return g;
+    bool todo = key >= 0;
+#pragma unroll
+    for (int r = 0; r < kGatherRounds; ++r) {
+        const uint64_t left = ballot(todo);
+        const int f = left ? __builtin_ctzll(left) : 0;
+        const bool same = todo && key == __builtin_amdgcn_readlane(key, f);
+        const uint64_t m = ballot(same);
+        if (same) g = Gather{f, (int)__popcll(m & lanes_below()), (int)__popcll(m)};
+        todo = todo && !same;
+    }
+    return g;
+}
+
 // x / n for x < 2^16 and 1 <= n <= 2^15, with m = div_magic(n).
 __device__ __forceinline__ uint32_t div_magic(int n) { return n > 1 ? 0xffffffffu / (uint32_t)n + 1u : 0u; }
 __device__ __forceinline__ int div_by(int x, uint32_t m) { return m ? (int)__umulhi((uint32_t)x, m) : x; }
@@ -363,20 +392,29 @@ __device__ __forceinline__ void decide_tile(const RouteParams& p, float* rows, u
     kmax = __builtin_amdgcn_readfirstlane(kmax);
     wave_lds_order();
     const int kv = v ? k : 0;
-    constexpr int kBatch = 8;
+    constexpr int kBatch = 4;
+    const bool few = p.select_mode != 0 || kb <= 4;
+    const Gather g0 = gather_key(v ? ks : -1, few);
     int r0 = 0;
-    if (v) r0 = atomicAdd(&p.bin_count[bin_counter(ks, bc, nbin)], 1);
+    if (v && g0.rank == 0) r0 = atomicAdd(&p.bin_count[bin_counter(ks, bc, nbin)], g0.count);
     for (int i0 = 0; i0 < kmax; i0 += kBatch) {
-        int q[kBatch], s[kBatch];
+        Gather g[kBatch];
+        int s[kBatch];
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) q[u] = (i0 + u < kv) ? irow[i0 + u] : 0;
+        for (int u = 0; u < kBatch; ++u) {
+            const bool in = i0 + u < kv;
+            const int key = in ? (irow[i0 + u] << kb) + kr : -1;
+            g[u] = gather_key(key, few);
+            s[u] = 0;
+            if (in && g[u].rank == 0) s[u] = atomicAdd(&p.bin_count[bin_counter(key, bc, nbin)], g[u].count);
+        }
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u)
-            if (i0 + u < kv) s[u] = atomicAdd(&p.bin_count[bin_counter((q[u] << kb) + kr, bc, nbin)], 1);
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u)
-            if (i0 + u < kv) irow[i0 + u] = s[u];
+        for (int u = 0; u < kBatch; ++u) {
+            const int slot = __shfl(s[u], g[u].lead) + g[u].rank;
+            if (i0 + u < kv) irow[i0 + u] = slot;
+        }
     }
+    r0 = __shfl(r0, g0.lead) + g0.rank;
     irow[K] = r0;
     wave_lds_order();
     const uint32_t mk1 = div_magic(K1);
