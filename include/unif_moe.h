@@ -296,8 +296,8 @@ int32_t unif_moe_block_forward(const unif_moe_config* cfg, const unif_moe_block*
  * the fp32 per-pair rows, which take dx per pair), and, for bf16 layers, a
  * second H-shaped buffer ((N(K+1) + 1) H bf16 values), a transposed copy of
  * W_down and 8 B N(K+1) bytes of per-block partial sums; for fp32 layers
- * the forward's 4 H N(K+1) bytes of activations, as many of their gradients,
- * and 8 B ceil(M / 64) N(K+1) bytes of partial sums. */
+ * 8 H N(K+1) bytes of activations and their gradients and
+ * 8 B ceil(M / 64) N(K+1) bytes of partial sums. */
 int32_t unif_moe_layer_backward_workspace_size(const unif_moe_config* cfg, size_t* bytes);
 
 /* Backward pass of the layer for a training step: the gradients of

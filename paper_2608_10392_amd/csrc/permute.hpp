@@ -354,7 +354,7 @@ __device__ __forceinline__ void scatter_tile(const PermuteParams& p, int q, cons
     const uint64_t m = v ? p.mask[t] : 0ull, rm = ~m & full;
     int* of = p.pair_of + (size_t)(v ? t : 0) * K1;
     const int* eid = p.eids + (size_t)(v ? t : 0) * K;
-    const bool slabs = p.slab_rows != nullptr;   // no slab lists for fp32 layers
+    const bool slabs = p.slab_rows != nullptr;   // none for fp32 layers that run pair by pair
     // The tile's first row in each slab (absolute), read while the pairs'
     // atomics are in flight.
     const int* tfirst = p.tile_cnt + (size_t)q * ncnt;

@@ -1028,11 +1028,11 @@ namespace {
 // Backward workspace: the forward's (routing record, pair tables, slab
 // lists; for bf16 layers its H buffer holds GELU(a), then w GELU(a), and its
 // fp16 W_down region the transposed W_up; its per-pair rows receive dx_pair),
-// then a second H-shaped buffer (GELU'(a), then d loss / da; fp32 for fp32
-// layers), for bf16 layers V^T, the per-(pair, block) partial sums of dy . E
+// then a second H-shaped buffer (GELU'(a), then d loss / da; for fp32 layers
+// both, act and da, in fp32), for bf16 layers V^T, the per-(pair, block) partial sums of dy . E
 // and the per-pair and per-token scalars.
 struct BwdPlan {
-    size_t fwd, da, gbuf, wdnT, dcp, dcoef, pw, dz, rpart, units, split, total;
+    size_t fwd, act, da, gbuf, wdnT, dcp, dcoef, pw, dz, rpart, units, split, total;
     int extra;   // units of the weight gradients on top of one per slab, at most
     int slots;   // partial sums of split weight-gradient slabs that fit the per-pair rows' region
 };
@@ -1046,6 +1046,7 @@ BwdPlan plan_backward(const Dims& m) {
     const size_t pmax = (size_t)m.N * m.K1;
     Carver cv;
     cv.cur = b.fwd;
+    b.act = cv.take(m.bf16 ? 0 : pmax * m.H * sizeof(float));
     b.da = cv.take(m.bf16 ? 0 : pmax * m.H * sizeof(float));
     b.gbuf = cv.take(m.bf16 ? (pmax + 1) * (size_t)m.H * 2 : 0);   // + the sink row
     b.wdnT = cv.take(m.bf16 ? (size_t)m.K1 * m.d * m.H * 2 : 0);
@@ -1275,6 +1276,7 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
         // 2. the same products in fp32: a = x K^T, dy V, dx_pair = da K
         f = f32_params(m, fp, ws, X, W_up, W_down);
         f.dY = static_cast<const float*>(dY);
+        f.act = reinterpret_cast<float*>(ws + bp.act);
         f.da = reinterpret_cast<float*>(ws + bp.da);
         f.dcp = dcp;
         f.pw = p.pw;
