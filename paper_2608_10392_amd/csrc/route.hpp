@@ -9,7 +9,8 @@
 //     exact and only the fp32 accumulation order differs from a sequential
 //     dot product. x W_shr is an fp32 dot product on the vector units.
 //   * fp32 tokens: the matrix cores in fp32 (v_mfma_f32_16x16x4_f32).
-// Decisions: one wave per tile of 64 tokens, one lane per token (decide_tile).
+// Decisions: one lane per token (decide_tile), the record and the counts by
+// the waves that share the tile of 64 tokens.
 // Every step is the paper's order in fp32 with explicitly rounded operations;
 // the rankings (ties toward the lower index) are sorting networks in the
 // lane's registers. Per tile, the rows per (expert, block) slab and the pairs
@@ -250,10 +251,10 @@ __host__ __device__ __forceinline__ int decide_length(int K, int B) {
     return n <= 8 ? 8 : n <= 16 ? 16 : (n <= 32 ? 32 : 64);
 }
 
-// Decisions of Sec. III-B and III-C for one tile of 64 tokens by one wave,
-// one lane per token. `rows` (LDS, stride p.lstride, odd) holds the tokens'
-// logits: shared demand, K experts, B priorities; `bits` is [B + K + 1]
-// words of LDS. Called by whole waves; tokens past the layer write nothing.
+// Decisions of Sec. III-B and III-C for one tile of 64 tokens, one lane of one
+// wave per token. `rows` (LDS, stride p.lstride, odd) holds the tokens'
+// logits: shared demand, K experts, B priorities; `bits` is tile_words
+// 8-byte words of LDS. Tokens past the layer write nothing.
 //   alpha, b    from the shared logit
 //   I_shr       the first b of the sorted priorities
 //   softmax     maximum, exponentials, their sum in index order, fp32
@@ -265,112 +266,138 @@ __host__ __device__ __forceinline__ int decide_length(int K, int B) {
 // is written (through LDS, so the stores are whole lines): 64 tokens cost
 // about as many wave instructions as the 4 tokens of a pass did when a group
 // of lanes shared a token and every broadcast was an LDS permute.
-template <int L>
-__device__ __forceinline__ void decide_tile(const RouteParams& p, float* rows, uint64_t* bits, int tile) {
+//
+// NW waves work on the tile (whole workgroups of NW waves, or NW = 1 and any
+// number of them): the first decides, then all of them write the record and
+// the tile's counts, and the others take the pair slots. Where there are few
+// tiles, what follows the decisions is a chain of instructions and round trips
+// on an otherwise idle compute unit (see kDecideWaves for what it costs).
+__host__ __device__ __forceinline__ int tile_words(int B, int K) { return B + K + 1 + kTileTok + kTileTok / 2; }
+
+template <int L, int NW>
+__device__ __forceinline__ void decide_tile(const RouteParams& p, float* rows, uint64_t* bits, int tile, int wave) {
     const int K = p.K, B = p.B, ls = p.lstride;
     const int lane = lane_id(), tok0 = tile * kTileTok, tok = tok0 + lane;
+    const int tid = wave * kWave + lane;   // among the tile's threads
+    constexpr int T = NW * kWave;
     const int ntok = min(kTileTok, p.N - tok0);
     float* row = rows + lane * ls;
-    const bool v = lane < ntok && (p.valid == nullptr || p.valid[tok] != 0);
-
-    // Eq. alpha (adaptive) or the fixed-alpha ablation.
-    float alpha;
-    if (p.alpha_mode == 0) {
-        const float sig = __fdiv_rn(1.0f, __fadd_rn(1.0f, expf(-row[0])));
-        alpha = __fadd_rn(p.tau, __fmul_rn(p.one_minus_2tau, sig));
-    } else {
-        alpha = p.alpha_fixed;
-    }
-    // Eq. block-count, half to even; clamp to [1, B-1] (adaptive), cap.
-    // (fminf/fmaxf drop a NaN alpha, so b stays in range for any input.)
-    int b = (int)rintf(fminf(fmaxf(__fmul_rn((float)B, alpha), 0.0f), (float)B));
-    if (p.alpha_mode == 0) b = min(max(b, 1), B - 1);
-    b = min(b, p.max_shared);
-
-    // Eq. block-priority / shared-indices: the b largest priorities, ties to
-    // the lower index.
-    const uint64_t full = (B == 64) ? ~0ull : ((1ull << B) - 1ull);
-    double a[L];
-    uint64_t mask;
-    if (p.select_mode == 0) {
-#pragma unroll
-        for (int c = 0; c < L; ++c) a[c] = (c < B) ? order_key<L>(row[1 + K + c], c) : 0.0;
-        sort_descending<0, L>(a);
-        mask = first_indices<L>(a, b);
-    } else {
-        mask = (b >= 64) ? ~0ull : ((1ull << b) - 1ull);
-    }
-
-    // Eq. residual-router-score: max-subtracted softmax, index-order sum.
-    float e[L];
-    float m = -INFINITY;
-#pragma unroll
-    for (int j = 0; j < L; ++j)
-        if (j < K) {
-            e[j] = row[1 + j];
-            m = fmaxf(m, e[j]);
-        }
-    float S = 0.f;
-#pragma unroll
-    for (int j = 0; j < L; ++j)
-        if (j < K) {
-            e[j] = expf(__fsub_rn(e[j], m));
-            S = __fadd_rn(S, e[j]);
-        }
-    // Eq. sorted-affinity: by decreasing affinity, ties to the lower index.
-#pragma unroll
-    for (int j = 0; j < L; ++j) a[j] = (j < K) ? order_key<L>(__fdiv_rn(e[j], S), j) : 0.0;
-    sort_descending<0, L>(a);
-    // The affinities back as floats (what rank_key maps to them), in order.
-    auto affinity = [&](int i) {
-        const uint32_t r = order_value(a[i]);
-        return __uint_as_float((r & 0x80000000u) ? r & 0x7fffffffu : ~r);
+    int* irow = reinterpret_cast<int*>(row);
+    const int* irows = reinterpret_cast<const int*>(rows);
+    // For the other waves: the tokens' I_shr, and their k (0: not valid).
+    uint64_t* const masks = bits + B + K + 1;
+    int* const ks_of = reinterpret_cast<int*>(masks + kTileTok);
+    const bool lead = NW == 1 || wave == 0;
+    // Orders the tile's LDS accesses between its waves.
+    auto settle = [&]() {
+        if constexpr (NW == 1) wave_lds_order();
+        else __syncthreads();
     };
-    // Eq. beta / expert-count: the smallest prefix reaching the target.
-    int k;
-    if (p.mass_mode == 2) {
-        k = p.fixed_k;
-    } else {
-        const float beta = __fsub_rn(1.0f, alpha);
-        const float target = (p.mass_mode == 0) ? fminf(beta, p.t_mass) : p.t_mass;
-        float P = 0.f;
-        bool reached = false;
-        k = 1;
+    const uint64_t full = (B == 64) ? ~0ull : ((1ull << B) - 1ull);
+    const bool v = lead && lane < ntok && (p.valid == nullptr || p.valid[tok] != 0);
+    double a[L];
+    uint64_t mask = 0, sel = 0;
+    int k = 0;
+    if (lead) {
+        // Eq. alpha (adaptive) or the fixed-alpha ablation.
+        float alpha;
+        if (p.alpha_mode == 0) {
+            const float sig = __fdiv_rn(1.0f, __fadd_rn(1.0f, expf(-row[0])));
+            alpha = __fadd_rn(p.tau, __fmul_rn(p.one_minus_2tau, sig));
+        } else {
+            alpha = p.alpha_fixed;
+        }
+        // Eq. block-count, half to even; clamp to [1, B-1] (adaptive), cap.
+        // (fminf/fmaxf drop a NaN alpha, so b stays in range for any input.)
+        int b = (int)rintf(fminf(fmaxf(__fmul_rn((float)B, alpha), 0.0f), (float)B));
+        if (p.alpha_mode == 0) b = min(max(b, 1), B - 1);
+        b = min(b, p.max_shared);
+
+        // Eq. block-priority / shared-indices: the b largest priorities, ties to
+        // the lower index.
+        if (p.select_mode == 0) {
+#pragma unroll
+            for (int c = 0; c < L; ++c) a[c] = (c < B) ? order_key<L>(row[1 + K + c], c) : 0.0;
+            sort_descending<0, L>(a);
+            mask = first_indices<L>(a, b);
+        } else {
+            mask = (b >= 64) ? ~0ull : ((1ull << b) - 1ull);
+        }
+
+        // Eq. residual-router-score: max-subtracted softmax, index-order sum.
+        float e[L];
+        float m = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < L; ++j)
+            if (j < K) {
+                e[j] = row[1 + j];
+                m = fmaxf(m, e[j]);
+            }
+        float S = 0.f;
+#pragma unroll
+        for (int j = 0; j < L; ++j)
+            if (j < K) {
+                e[j] = expf(__fsub_rn(e[j], m));
+                S = __fadd_rn(S, e[j]);
+            }
+        // Eq. sorted-affinity: by decreasing affinity, ties to the lower index.
+#pragma unroll
+        for (int j = 0; j < L; ++j) a[j] = (j < K) ? order_key<L>(__fdiv_rn(e[j], S), j) : 0.0;
+        sort_descending<0, L>(a);
+        // The affinities back as floats (what rank_key maps to them), in order.
+        auto affinity = [&](int i) {
+            const uint32_t r = order_value(a[i]);
+            return __uint_as_float((r & 0x80000000u) ? r & 0x7fffffffu : ~r);
+        };
+        // Eq. beta / expert-count: the smallest prefix reaching the target.
+        if (p.mass_mode == 2) {
+            k = p.fixed_k;
+        } else {
+            const float beta = __fsub_rn(1.0f, alpha);
+            const float target = (p.mass_mode == 0) ? fminf(beta, p.t_mass) : p.t_mass;
+            float P = 0.f;
+            bool reached = false;
+            k = 1;
+#pragma unroll
+            for (int i = 0; i < L; ++i)
+                if (i < K) {
+                    P = __fadd_rn(P, affinity(i));
+                    reached = reached || P >= target;
+                    k += reached ? 0 : 1;
+                }
+            k = min(k, K);
+        }
+        sel = v ? first_indices<L>(a, k) : 0ull;   // bit j: expert j + 1
+
+        // The record. Rows of K values per token go through the token's LDS row.
+        if (lane < ntok) {
+            p.alpha[tok] = v ? alpha : 0.f;
+            p.nsh[tok] = v ? b : 0;
+            p.mask[tok] = v ? mask : 0ull;
+            p.nres[tok] = v ? k : 0;
+        }
 #pragma unroll
         for (int i = 0; i < L; ++i)
-            if (i < K) {
-                P = __fadd_rn(P, affinity(i));
-                reached = reached || P >= target;
-                k += reached ? 0 : 1;
-            }
-        k = min(k, K);
-    }
-    const uint64_t sel = v ? first_indices<L>(a, k) : 0ull;   // bit j: expert j + 1
-
-    // The record. Rows of K values per token go through the token's LDS row.
-    if (lane < ntok) {
-        p.alpha[tok] = v ? alpha : 0.f;
-        p.nsh[tok] = v ? b : 0;
-        p.mask[tok] = v ? mask : 0ull;
-        p.nres[tok] = v ? k : 0;
+            if (i < K) row[i] = v ? affinity(i) : 0.f;
+        if constexpr (NW > 1) {
+            masks[lane] = mask;
+            ks_of[lane] = v ? k : 0;
+        }
     }
     const uint32_t mk = div_magic(K);
-#pragma unroll
-    for (int i = 0; i < L; ++i)
-        if (i < K) row[i] = v ? affinity(i) : 0.f;
-    wave_lds_order();
-    for (int x = lane; x < ntok * K; x += kWave) {
+    settle();
+    for (int x = tid; x < ntok * K; x += T) {
         const int t = div_by(x, mk);
         p.wts[(size_t)tok0 * K + x] = rows[t * ls + x - t * K];
     }
-    wave_lds_order();
-    int* irow = reinterpret_cast<int*>(row);
-    const int* irows = reinterpret_cast<const int*>(rows);
+    settle();
+    if (lead) {
 #pragma unroll
-    for (int i = 0; i < L; ++i)
-        if (i < K) irow[i] = v ? 1 + order_index<L>(a[i]) : -1;
-    wave_lds_order();
-    for (int x = lane; x < ntok * K; x += kWave) {
+        for (int i = 0; i < L; ++i)
+            if (i < K) irow[i] = v ? 1 + order_index<L>(a[i]) : -1;
+    }
+    settle();
+    for (int x = tid; x < ntok * K; x += T) {
         const int t = div_by(x, mk);
         p.eids[(size_t)tok0 * K + x] = irows[t * ls + x - t * K];
     }
@@ -382,77 +409,88 @@ __device__ __forceinline__ void decide_tile(const RouteParams& p, float* rows, u
     // the scatter needs no atomics; slots inside a bin follow the order the
     // atomics land in, and no result depends on it (every GEMM row is
     // computed from its own pair). The atomics of a batch are all issued
-    // before a slot is stored.
-    const int kb = p.key_bits, K1 = K + 1;
-    const int ks = mask_key(mask, B, kb), kr = mask_key(~mask & full, B, kb);
-    const int bc = tile % kBinCopies, nbin = K1 << kb;
-    int kmax = v ? k : 0;
+    // before a slot is stored. With several waves the first one makes the
+    // tile's bit matrices meanwhile, and the others take a batch each in turn.
+    const int kb = p.key_bits, K1 = K + 1, nbin = K1 << kb;
+    settle();
+    if (NW == 1 || !lead) {
+        const int kv = NW == 1 ? (v ? k : 0) : ks_of[lane];
+        const uint64_t ms = NW == 1 ? mask : masks[lane];
+        const bool valid = kv > 0;   // k >= 1 for every valid token
+        const int ks = mask_key(ms, B, kb), kr = mask_key(~ms & full, B, kb);
+        const int bc = tile % kBinCopies;
+        int kmax = kv;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) kmax = max(kmax, __shfl_xor(kmax, o));
-    kmax = __builtin_amdgcn_readfirstlane(kmax);
-    wave_lds_order();
-    const int kv = v ? k : 0;
-    constexpr int kBatch = 4;
-    const bool few = p.select_mode != 0 || kb <= 4;
-    const Gather g0 = gather_key(v ? ks : -1, few);
-    int r0 = 0;
-    if (v && g0.rank == 0) r0 = atomicAdd(&p.bin_count[bin_counter(ks, bc, nbin)], g0.count);
-    for (int i0 = 0; i0 < kmax; i0 += kBatch) {
-        Gather g[kBatch];
-        int s[kBatch];
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const bool in = i0 + u < kv;
-            const int key = in ? (irow[i0 + u] << kb) + kr : -1;
-            g[u] = gather_key(key, few);
-            s[u] = 0;
-            if (in && g[u].rank == 0) s[u] = atomicAdd(&p.bin_count[bin_counter(key, bc, nbin)], g[u].count);
+        for (int o = 32; o > 0; o >>= 1) kmax = max(kmax, __shfl_xor(kmax, o));
+        kmax = __builtin_amdgcn_readfirstlane(kmax);
+        constexpr int kBatch = 4, WB = NW == 1 ? 1 : NW - 1;   // waves that take batches
+        const int w = NW == 1 ? 0 : wave - 1;
+        const bool few = p.select_mode != 0 || kb <= 4;
+        Gather g0{lane, 0, 1};
+        int r0 = 0;
+        if (w == 0) {
+            g0 = gather_key(valid ? ks : -1, few);
+            if (valid && g0.rank == 0) r0 = atomicAdd(&p.bin_count[bin_counter(ks, bc, nbin)], g0.count);
         }
+        for (int i0 = w * kBatch; i0 < kmax; i0 += WB * kBatch) {
+            Gather g[kBatch];
+            int s[kBatch];
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const int slot = __shfl(s[u], g[u].lead) + g[u].rank;
-            if (i0 + u < kv) irow[i0 + u] = slot;
+            for (int u = 0; u < kBatch; ++u) {
+                const bool in = i0 + u < kv;
+                const int key = in ? (irow[i0 + u] << kb) + kr : -1;
+                g[u] = gather_key(key, few);
+                s[u] = 0;
+                if (in && g[u].rank == 0) s[u] = atomicAdd(&p.bin_count[bin_counter(key, bc, nbin)], g[u].count);
+            }
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const int slot = __shfl(s[u], g[u].lead) + g[u].rank;
+                if (i0 + u < kv) irow[i0 + u] = slot;
+            }
+        }
+        if (w == 0) {
+            r0 = __shfl(r0, g0.lead) + g0.rank;
+            irow[K] = r0;
         }
     }
-    r0 = __shfl(r0, g0.lead) + g0.rank;
-    irow[K] = r0;
-    wave_lds_order();
+    // The tile's bit matrices: bits[c] the tokens that share block c,
+    // bits[B + e] the tokens on expert e.
+    if (lead && p.tile_cnt != nullptr) {
+        uint64_t mine = 0;
+        const uint64_t vm = v ? mask : 0ull;
+        for (int c = 0; c < B; ++c) {
+            const uint64_t t = ballot((vm >> c) & 1ull);
+            mine = (lane == c) ? t : mine;
+        }
+        if (lane < B) bits[lane] = mine;
+        const uint64_t all = ballot(v);
+        for (int j = 0; j < K; ++j) {
+            const uint64_t t = ballot((sel >> j) & 1ull);
+            mine = (lane == j) ? t : mine;
+        }
+        if (lane < K) bits[B + 1 + lane] = mine;
+        if (lane == 0) bits[B] = all;
+    }
+    settle();
     const uint32_t mk1 = div_magic(K1);
-    for (int x = lane; x < ntok * K1; x += kWave) {
+    for (int x = tid; x < ntok * K1; x += T) {
         const int t = div_by(x, mk1), j = x - t * K1;
         p.pair_rank[(size_t)tok0 * K1 + x] = irows[t * ls + (j == 0 ? K : j - 1)];
     }
     if (p.tile_cnt == nullptr) return;
 
-    // The tile's counts (rows per slab: the shared expert on I_shr, each
-    // selected residual expert on I_res; pairs per expert) from the tile's
-    // bit matrices: bits[c] the tokens that share block c, bits[B + e] the
-    // tokens on expert e.
-    uint64_t mine = 0;
-    const uint64_t vm = v ? mask : 0ull;
-    for (int c = 0; c < B; ++c) {
-        const uint64_t t = ballot((vm >> c) & 1ull);
-        mine = (lane == c) ? t : mine;
-    }
-    if (lane < B) bits[lane] = mine;
-    if (lane == 0) bits[B] = 0;
-    const uint64_t all = ballot(v);
-    for (int j = 0; j < K; ++j) {
-        const uint64_t t = ballot((sel >> j) & 1ull);
-        mine = (lane == j) ? t : mine;
-    }
-    if (lane < K) bits[B + 1 + lane] = mine;
-    if (lane == 0) bits[B] = all;
-    wave_lds_order();
+    // The tile's counts: rows per slab (the shared expert on I_shr, each
+    // selected residual expert on I_res) and pairs per expert.
     const int nslab = K1 * B, ncnt = nslab + K1;
     const uint32_t mb = div_magic(B);
     int* cnt = p.tile_cnt + (size_t)tile * ncnt;
-    for (int x = lane; x < nslab; x += kWave) {
+    for (int x = tid; x < nslab; x += T) {
         const int ee = div_by(x, mb);
         const uint64_t sh = bits[x - ee * B], te = bits[B + ee];
         cnt[x] = __popcll(te & (ee == 0 ? sh : ~sh));
     }
-    for (int x = lane; x < K1; x += kWave) {
+    for (int x = tid; x < K1; x += T) {
         const int c = __popcll(bits[B + x]);
         cnt[nslab + x] = c;
         // Pairs per expert also into the totals (few atomics, spread).
@@ -461,12 +499,13 @@ __device__ __forceinline__ void decide_tile(const RouteParams& p, float* rows, u
 }
 
 // decide_tile with the list length of the layer (see decide_length).
-__device__ __forceinline__ void decide_tile_any(const RouteParams& p, float* rows, uint64_t* bits, int tile) {
+template <int NW>
+__device__ __forceinline__ void decide_tile_any(const RouteParams& p, float* rows, uint64_t* bits, int tile, int wave) {
     switch (decide_length(p.K, p.B)) {
-        case 8: decide_tile<8>(p, rows, bits, tile); break;
-        case 16: decide_tile<16>(p, rows, bits, tile); break;
-        case 32: decide_tile<32>(p, rows, bits, tile); break;
-        default: decide_tile<64>(p, rows, bits, tile); break;
+        case 8: decide_tile<8, NW>(p, rows, bits, tile, wave); break;
+        case 16: decide_tile<16, NW>(p, rows, bits, tile, wave); break;
+        case 32: decide_tile<32, NW>(p, rows, bits, tile, wave); break;
+        default: decide_tile<64, NW>(p, rows, bits, tile, wave); break;
     }
 }
 
@@ -650,7 +689,7 @@ __global__ __launch_bounds__(kSplitWaves * 64) void route_split_k_kernel(RoutePa
         lds_route[x] = v;
     }
     __syncthreads();
-    if (wave == 0) decide_tile_any(p, lds_route, reinterpret_cast<uint64_t*>(lds_route + kSplitWaves * part), tile);
+    decide_tile_any<kSplitWaves>(p, lds_route, reinterpret_cast<uint64_t*>(lds_route + kSplitWaves * part), tile, wave);
 }
 
 // bf16 routers of any width over many tokens: 4 waves, one 64-token tile
@@ -784,8 +823,8 @@ __global__ __launch_bounds__(kWideWaves * 64, NCT <= 4 ? 2 : 1) void route_wide_
     put_logits<NCT>(rows, ls, acc, sh);
     wave_lds_order();
     if (tok0 >= p.N) return;
-    uint64_t* bits = reinterpret_cast<uint64_t*>(lds_route + kWideWaves * kTileTok * ls) + wave * (p.B + p.K + 1);
-    decide_tile_any(p, rows, bits, tile);
+    uint64_t* bits = reinterpret_cast<uint64_t*>(lds_route + kWideWaves * kTileTok * ls) + wave * tile_words(p.B, p.K);
+    decide_tile_any<1>(p, rows, bits, tile, 0);
 }
 
 // Logits of bf16 tokens when the router fits in registers (1 + K + B <= 32
@@ -886,18 +925,26 @@ __global__ __launch_bounds__(kRpThreads) void route_logits_kernel(RouteParams p,
 }
 
 // Decisions from the logits route_logits_kernel wrote ([N][lstride]), one
-// 64-token tile per one-wave workgroup. The last p.cvt_blocks workgroups do
-// the launch's copy job instead.
-template <int L>
-__global__ __launch_bounds__(64) void route_decide_kernel(RouteParams p, const float* __restrict__ logits) {
+// 64-token tile per workgroup of NW waves: kDecideWaves while the tiles are
+// few (see kDecideTiles), else one. A forward's decisions of 20,000 tokens
+// (313 tiles, K = 16, B = 8), which also take the pair slots and the counts,
+// need 24.9 us from one wave per tile, and four take 4 to 6 us off the call
+// (17,000 tokens of d = 512: 282 -> 277 us). The last p.cvt_blocks workgroups
+// do the launch's copy job instead.
+constexpr int kDecideWaves = 4;
+
+template <int L, int NW>
+__global__ __launch_bounds__(NW * 64) void route_decide_kernel(RouteParams p, const float* __restrict__ logits) {
     if (route_copy_role(p)) return;
     extern __shared__ __attribute__((aligned(16))) float lds_dec[];
     const int tile = blockIdx.x, tok0 = tile * kTileTok, ntok = min(kTileTok, p.N - tok0);
+    const int wave = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const float* src = logits + (size_t)tok0 * p.lstride;
     // Rows past the layer keep whatever LDS holds; they are not decided.
     batched_copy(ntok * p.lstride, [&](int i) { return src[i]; }, [&](int i, float v) { lds_dec[i] = v; });
-    wave_lds_order();
-    decide_tile<L>(p, lds_dec, reinterpret_cast<uint64_t*>(lds_dec + kTileTok * p.lstride), tile);
+    if constexpr (NW == 1) wave_lds_order();
+    else __syncthreads();
+    decide_tile<L, NW>(p, lds_dec, reinterpret_cast<uint64_t*>(lds_dec + kTileTok * p.lstride), tile, wave);
 }
 
 }  // namespace unifmoe

@@ -56,6 +56,11 @@ constexpr size_t kLdsLimit = 160 * 1024;
 // Up to this many 64-token tiles the routing runs in one launch of one tile
 // per workgroup (route_split_k_kernel).
 constexpr int kSplitKTiles = 256;
+// Up to this many tiles of a decisions launch kDecideWaves waves share a tile,
+// past it (5 tiles per compute unit) the tiles fill the chip and one wave does
+// it all: 70,000 tokens of d = 768, K = B = 16 (1,094 tiles) 47.4 us by one
+// wave and 45.0 by four, 100,000 tokens (1,563 tiles) 56.1 against 59.5 us.
+constexpr int kDecideTiles = 1280;
 
 // Expert-GEMM tile shapes, one workgroup of 8 waves per CU. Up: 256 or 384
 // gathered rows x the whole block width M. Down: see down_shape.
@@ -156,7 +161,7 @@ size_t tile_counters(const Dims& m) { return (size_t)m.nslab + m.K1; }
 // space with its stages of router rows), then the bit matrices of the tiles a
 // workgroup decides.
 size_t tile_logits_bytes(const Dims& m) { return sizeof(float) * kTileTok * (size_t)m.lstride; }
-size_t tile_bits_bytes(const Dims& m) { return sizeof(uint64_t) * (size_t)(m.B + m.K1); }
+size_t tile_bits_bytes(const Dims& m) { return sizeof(uint64_t) * (size_t)tile_words(m.B, m.K); }
 size_t route_split_k_lds_bytes(const Dims& m) { return kSplitWaves * tile_logits_bytes(m) + tile_bits_bytes(m); }
 size_t route_wide_lds_bytes(const Dims& m) {
     return std::max((size_t)2 * (3 * m.NLP * 128 + 256), kWideWaves * (tile_logits_bytes(m) + tile_bits_bytes(m)));
@@ -477,17 +482,18 @@ int32_t launch_route(const Dims& m, RouteParams rp, const float* Wr, const float
             default: return UNIF_EUNSUPPORTED;
         }
         void (*dk)(RouteParams, const float*) = nullptr;
+        const int dw = ntiles <= kDecideTiles ? kDecideWaves : 1;
         switch (decide_length(m.K, m.B)) {
-            case 8: dk = route_decide_kernel<8>; break;
-            case 16: dk = route_decide_kernel<16>; break;
-            default: dk = route_decide_kernel<32>; break;   // K + B <= 32
+            case 8: dk = dw == 1 ? route_decide_kernel<8, 1> : route_decide_kernel<8, kDecideWaves>; break;
+            case 16: dk = dw == 1 ? route_decide_kernel<16, 1> : route_decide_kernel<16, kDecideWaves>; break;
+            default: dk = dw == 1 ? route_decide_kernel<32, 1> : route_decide_kernel<32, kDecideWaves>; break;   // K + B <= 32
         }
         const size_t l1 = route_logits_lds_bytes(m), l2 = route_decide_lds_bytes(m);
         if (allow_lds(lk, l1) != UNIF_OK || allow_lds(dk, l2) != UNIF_OK) return UNIF_EDEVICE;
-        rp.cvt_blocks = copy_blocks(64);
+        rp.cvt_blocks = copy_blocks(64 * dw);
         lk<<<std::min(cus, ntiles), kRpThreads, l1, st>>>(rp, logits);
         UNIF_LAUNCH_CHECK();
-        dk<<<ntiles + rp.cvt_blocks, 64, l2, st>>>(rp, logits);
+        dk<<<ntiles + rp.cvt_blocks, 64 * dw, l2, st>>>(rp, logits);
         UNIF_LAUNCH_CHECK();
         return UNIF_OK;
     }

@@ -11,6 +11,7 @@ import pytest
 import oracle.unif_moe_oracle as O
 from synth import generate, get_config, layer_config
 from tests import parity
+from tests.test_gpu_parity import run_case
 
 pytestmark = pytest.mark.gpu
 
@@ -55,21 +56,56 @@ def test_route(name, padded):
           f"p err {s['max_p_err']:.1e}", flush=True)
 
 
-def test_route_ties_and_prefix():
+# The same launches in a forward, where the decisions also take the pairs'
+# slots and the tile's counts: every row of the expert FFNs depends on them.
+# One tile, the last and the first sizes of each launch (256 tiles; 1,280
+# tiles, past which one wave does a tile), lists of 8 to 64 entries, and the
+# slots gathered over a wave (prefix selection, at most 4 mask bits).
+FORWARDS = {
+    "one_tile": (33, 12, 8, {}),
+    "split_last": (16384, 16, 16, {}),
+    "held_first": (16385, 16, 16, {}),
+    "held_8_first": (16385, 8, 8, {}),
+    "held_prefix": (16400, 9, 12, dict(select_mode="prefix")),
+    "held_4_blocks": (16400, 16, 4, {}),
+    "held_topk": (16400, 16, 8, dict(mass_mode="topk", fixed_k=16)),
+    "held_last_shared": (1280 * 64, 16, 8, {}),
+    "held_one_wave": (1280 * 64 + 1, 16, 8, {}),
+    "wide_33_columns": (16385, 16, 17, {}),
+    "wide_65_columns": (16385, 63, 2, {}),
+    "wide_128_columns": (16641, 64, 64, {}),
+}
+
+
+@pytest.mark.parametrize("name", list(FORWARDS))
+def test_forward(name):
+    N, K, B, modes = FORWARDS[name]
+    g = generate(get_config("vit_s16", n_tokens=N, d_model=128, n_experts=K, n_blocks=B, block_width=64, max_shared=B,
+                            **modes))
+    g["valid"] = (np.arange(N) % 7 != 3).astype(np.uint8)
+    run_case(g, f"routing launch {name}", n_sample=96)
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("select", ["prototype", "prefix"])
+def test_route_ties_and_prefix(select):
     """Equal affinities and priorities rank by index: tokens of zeros tie
-    everywhere, so I_shr is the first b blocks and q = 1..K in order."""
+    everywhere, so I_shr is the first b blocks and q = 1..K in order. With
+    prefix selection I_shr is the first b blocks of every token."""
     from paper_2608_10392_amd.layer import DeviceLayer
     N, d, K, B = 129, 64, 12, 20
-    g = generate(get_config("vit_s16", n_tokens=N, d_model=d, n_experts=K, n_blocks=B, block_width=64, max_shared=B),
-                 weights=False)
+    g = generate(get_config("vit_s16", n_tokens=N, d_model=d, n_experts=K, n_blocks=B, block_width=64, max_shared=B,
+                            select_mode=select), weights=False)
     X = g["X"].copy()
     X[::2] = 0
     dev = DeviceLayer(layer_config(g["cfg"]), X, None, g["W_router"], g["prototypes"])
     dev.route()
     torch.cuda.synchronize()
     r = dev.routing_numpy()
-    for t in range(0, N, 2):
+    for t in range(N):
         b = int(r["n_shared"][t])
-        assert int(r["shared_mask"][t]) == (1 << b) - 1
-        assert r["expert_ids"][t].tolist() == list(range(1, K + 1))
-        assert np.all(r["weights"][t] == r["weights"][t, 0])
+        if t % 2 == 0 or select == "prefix":
+            assert int(r["shared_mask"][t]) == (1 << b) - 1
+        if t % 2 == 0:
+            assert r["expert_ids"][t].tolist() == list(range(1, K + 1))
+            assert np.all(r["weights"][t] == r["weights"][t, 0])
