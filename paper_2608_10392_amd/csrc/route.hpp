@@ -541,11 +541,10 @@ __device__ __forceinline__ void put_logits(float* P, int ls, const f32x4 (&acc)[
 // One tile per workgroup of kSplitWaves waves, which share the contraction;
 // the partial logits are summed in wave order and wave 0 decides the tile.
 // For few tiles the chain of k steps of one wave sets the time, and this
-// splits it: up to 256 tiles (one per compute unit) it is as fast as either
-// other form or faster (16,384 tokens of d = 768, K = B = 16: 21 us against
-// 25 us in two launches; d = 1024, K = B = 32: 38 against 46 us), past that
-// the router rows it re-reads per tile make it slower (32,768: 39 against 32
-// us, 71 against 47 us). NCT: 16-column tiles of the bf16 router; 0: fp32 tokens. The
+// splits it (16,384 tokens of d = 768, K = B = 16: 21 us against 25 us in two
+// launches; d = 1024, K = B = 32: 38 against 46 us); with more tiles the router
+// rows it re-reads per tile make it slower (see kSplitKTiles).
+// NCT: 16-column tiles of the bf16 router; 0: fp32 tokens. The
 // last p.cvt_blocks workgroups do the launch's copy job.
 constexpr int kSplitWaves = 4;
 

@@ -54,8 +54,15 @@ constexpr int kKeyBitsMax = 10;
 constexpr int kPhaseEvents = 7;   // unif_moe_layer_forward_profiled
 constexpr size_t kLdsLimit = 160 * 1024;
 // Up to this many 64-token tiles the routing runs in one launch of one tile
-// per workgroup (route_split_k_kernel).
-constexpr int kSplitKTiles = 256;
+// per workgroup (route_split_k_kernel): one per compute unit, or two where the
+// router has at most 16 columns, so that a tile reads little of it and two fit
+// a compute unit. d = 384, K = 6, B = 8: 25,000 tokens 14.5 us in one launch
+// and 16.9 in two, 50,000 tokens 22.6 and 22.3; d = 4096, K = B = 4: 25,000
+// tokens 64 us against 90 with the router streamed through LDS for four tiles
+// at once, which leaves three compute units in four idle there, 50,000 tokens
+// 144 against 129. Wider routers past 256 tiles: 16,385 tokens of d = 768,
+// K = B = 16 33 us against 25, d = 1024, K = B = 32 63 against 50.
+constexpr int kSplitKTiles = 256, kSplitKTilesNarrow = 512;
 // Up to this many tiles of a decisions launch kDecideWaves waves share a tile,
 // past it (5 tiles per compute unit) the tiles fill the chip and one wave does
 // it all: 70,000 tokens of d = 768, K = B = 16 (1,094 tiles) 47.4 us by one
@@ -461,13 +468,14 @@ int32_t launch_route(const Dims& m, RouteParams rp, const float* Wr, const float
         UNIF_LAUNCH_CHECK();
     }
     const int ntiles = ceil_div(m.N, kTileTok), nct = m.NLP / 16, cus = cu_count();
+    const bool split_k = ntiles <= (nct == 1 ? kSplitKTilesNarrow : kSplitKTiles);
     // The copy job's share of a launch: at most 8 waves per compute unit.
     auto copy_blocks = [&](int threads) {
         return (int)std::min<size_t>(ceil_div_sz(rp.cvt_n8, threads), (size_t)cus * (512 / threads));
     };
     // bf16 routers of at most 32 columns: logits (router in registers), then
     // decisions.
-    if (split_route_cols(m) > 0 && logits != nullptr && ntiles > kSplitKTiles) {
+    if (split_route_cols(m) > 0 && logits != nullptr && !split_k) {
         void (*lk)(RouteParams, float*) = nullptr;
         const int kpw = ceil_div(m.d / 32, kRpWaves);
         switch (nct * 4 + kpw) {
@@ -498,7 +506,7 @@ int32_t launch_route(const Dims& m, RouteParams rp, const float* Wr, const float
         return UNIF_OK;
     }
     // Logits and decisions in one launch.
-    const bool wide = m.bf16 && ntiles > kSplitKTiles;
+    const bool wide = m.bf16 && !split_k;
     void (*kern)(RouteParams) = route_split_k_kernel<0>;
     if (m.bf16) {
         switch (nct) {

@@ -1,6 +1,6 @@
 """The routing launches at the sizes where they change over, against the
-oracle (MI355X only): one tile per workgroup up to 256 tiles of 64 tokens,
-past that the register-held router (at most 32 columns, d <= 1024) or the
+oracle (MI355X only): one tile per workgroup up to 256 tiles of 64 tokens
+(512 where the router has at most 16 columns), past that the register-held router (at most 32 columns, d <= 1024) or the
 streamed one, and the fp32 logits at row lengths that are not a multiple of
 any vector width. Decisions are compared by the protocol of tests/parity.py
 (exact beyond a margin of 1e-4; alpha and affinities within 1e-5, the fp32
@@ -26,6 +26,9 @@ CASES = {
     "held_16_columns": (16385, 96, 8, 8, "bf16"),
     "held_32_columns": (16449, 1024, 2, 30, "bf16"),
     "wide_d_over_1024": (16385, 1056, 3, 4, "bf16"),
+    "split_narrow_last": (32768, 160, 7, 9, "bf16"),
+    "held_narrow_first": (32769, 160, 7, 9, "bf16"),
+    "wide_narrow_first": (32769, 1056, 3, 4, "bf16"),
     "wide_33_columns": (16385, 96, 16, 17, "bf16"),
     "wide_64_columns": (16700, 128, 32, 32, "bf16"),
     "wide_65_columns": (16385, 32, 64, 2, "bf16"),
@@ -65,7 +68,8 @@ FORWARDS = {
     "one_tile": (33, 12, 8, {}),
     "split_last": (16384, 16, 16, {}),
     "held_first": (16385, 16, 16, {}),
-    "held_8_first": (16385, 8, 8, {}),
+    "split_narrow_last": (32768, 8, 8, {}),
+    "held_narrow_first": (32769, 8, 8, {}),
     "held_prefix": (16400, 9, 12, dict(select_mode="prefix")),
     "held_4_blocks": (16400, 16, 4, {}),
     "held_topk": (16400, 16, 8, dict(mass_mode="topk", fixed_k=16)),
