@@ -272,7 +272,9 @@ __host__ __device__ __forceinline__ int decide_length(int K, int B) {
 // the tile's counts, and the others take the pair slots. Where there are few
 // tiles, what follows the decisions is a chain of instructions and round trips
 // on an otherwise idle compute unit (see kDecideWaves for what it costs).
-__host__ __device__ __forceinline__ int tile_words(int B, int K) { return B + K + 1 + kTileTok + kTileTok / 2; }
+__host__ __device__ __forceinline__ int tile_words(int B, int K, int nw) {
+    return B + K + 1 + (nw > 1 ? kTileTok + kTileTok / 2 : 0);
+}
 
 template <int L, int NW>
 __device__ __forceinline__ void decide_tile(const RouteParams& p, float* rows, uint64_t* bits, int tile, int wave) {
@@ -822,7 +824,7 @@ __global__ __launch_bounds__(kWideWaves * 64, NCT <= 4 ? 2 : 1) void route_wide_
     put_logits<NCT>(rows, ls, acc, sh);
     wave_lds_order();
     if (tok0 >= p.N) return;
-    uint64_t* bits = reinterpret_cast<uint64_t*>(lds_route + kWideWaves * kTileTok * ls) + wave * tile_words(p.B, p.K);
+    uint64_t* bits = reinterpret_cast<uint64_t*>(lds_route + kWideWaves * kTileTok * ls) + wave * tile_words(p.B, p.K, 1);
     decide_tile_any<1>(p, rows, bits, tile, 0);
 }
 

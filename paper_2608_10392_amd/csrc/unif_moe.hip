@@ -168,13 +168,13 @@ size_t tile_counters(const Dims& m) { return (size_t)m.nslab + m.K1; }
 // space with its stages of router rows), then the bit matrices of the tiles a
 // workgroup decides.
 size_t tile_logits_bytes(const Dims& m) { return sizeof(float) * kTileTok * (size_t)m.lstride; }
-size_t tile_bits_bytes(const Dims& m) { return sizeof(uint64_t) * (size_t)tile_words(m.B, m.K); }
-size_t route_split_k_lds_bytes(const Dims& m) { return kSplitWaves * tile_logits_bytes(m) + tile_bits_bytes(m); }
+size_t tile_bits_bytes(const Dims& m, int nw) { return sizeof(uint64_t) * (size_t)tile_words(m.B, m.K, nw); }
+size_t route_split_k_lds_bytes(const Dims& m) { return kSplitWaves * tile_logits_bytes(m) + tile_bits_bytes(m, kSplitWaves); }
 size_t route_wide_lds_bytes(const Dims& m) {
-    return std::max((size_t)2 * (3 * m.NLP * 128 + 256), kWideWaves * (tile_logits_bytes(m) + tile_bits_bytes(m)));
+    return std::max((size_t)2 * (3 * m.NLP * 128 + 256), kWideWaves * (tile_logits_bytes(m) + tile_bits_bytes(m, 1)));
 }
 size_t route_logits_lds_bytes(const Dims& m) { return kRpWaves * tile_logits_bytes(m); }
-size_t route_decide_lds_bytes(const Dims& m) { return tile_logits_bytes(m) + tile_bits_bytes(m); }
+size_t route_decide_lds_bytes(const Dims& m, int nw) { return tile_logits_bytes(m) + tile_bits_bytes(m, nw); }
 // Logits of the split routing path (bf16 routers of <= 32 columns, d <= 1024):
 // 1 + 16 NCT fp32 values per token, or 0 when the path does not apply.
 int split_route_cols(const Dims& m) {
@@ -496,7 +496,7 @@ int32_t launch_route(const Dims& m, RouteParams rp, const float* Wr, const float
             case 16: dk = dw == 1 ? route_decide_kernel<16, 1> : route_decide_kernel<16, kDecideWaves>; break;
             default: dk = dw == 1 ? route_decide_kernel<32, 1> : route_decide_kernel<32, kDecideWaves>; break;   // K + B <= 32
         }
-        const size_t l1 = route_logits_lds_bytes(m), l2 = route_decide_lds_bytes(m);
+        const size_t l1 = route_logits_lds_bytes(m), l2 = route_decide_lds_bytes(m, dw);
         if (allow_lds(lk, l1) != UNIF_OK || allow_lds(dk, l2) != UNIF_OK) return UNIF_EDEVICE;
         rp.cvt_blocks = copy_blocks(64 * dw);
         lk<<<std::min(cus, ntiles), kRpThreads, l1, st>>>(rp, logits);
