@@ -69,19 +69,29 @@ constexpr int kSplitKTiles = 256, kSplitKTilesNarrow = 512;
 // wave and 45.0 by four, 100,000 tokens (1,563 tiles) 56.1 against 59.5 us.
 constexpr int kDecideTiles = 1280;
 
-// Expert-GEMM tile shapes, one workgroup of 8 waves per CU. Up: 256 or 384
-// gathered rows x the whole block width M. Down: see down_shape.
+// Expert-GEMM tile shapes, one workgroup of 8 waves per CU. Down: see
+// down_shape. Up: 128, 256 or 384 gathered rows x the whole block width M.
 // Up tiles are 384 rows when the block is at most 192 wide and no stage is
 // padding (d >= 256): their accumulators and fragments then still fit two
-// waves per SIMD without spills. Else 256. Small calls, whose slabs are
+// waves per SIMD. Else 256. Small calls, whose slabs are
 // estimated (4 pairs per token, half of the blocks each) to fill no more than
 // one such tile, take 128: the rows a slab lacks cost a tile as much as those
 // it has, in products and above all in the GELU of the epilogue (one image of
-// a DeiT-S layer, 56 rows a slab: 20.8 -> 11.3 us).
-constexpr int kUpSmallRows = 384;
-int up_tm(int N, int K1, int M, int d) {
+// a DeiT-S layer, 56 rows a slab: 20.8 -> 11.3 us; whole calls at 32 to 380
+// estimated rows a slab: M = 192 and 128 0 to 12% faster, few slabs of any
+// width 5 to 9%).
+// Many slabs of 64 or 256 channels take 128 only up to 64 estimated rows: past
+// that the 128-row tiles no longer run at once, and a 256-channel tile is 256
+// rows otherwise, which wastes less, while a 64-channel one is too short for
+// its own start (K = 16, B = 12, M = 256, d = 1152: 64 rows 178 us against 184,
+// 128 rows 234 against 218, 380 rows 347 against 316; K = 32, B = 16, M = 64,
+// d = 512: 64 rows 179 against 184, 128 rows 223 against 216, 380 rows 334
+// against 320).
+constexpr int kUpSmallRows = 384, kUpSmallRowsMany = 64, kUpManySlabs = 128;
+int up_tm(int N, int K1, int B, int M, int d) {
     if (d < 256) return 256;
-    if ((int64_t)N * std::min(K1, 4) <= (int64_t)2 * kUpSmallRows * K1) return 128;
+    const int rows = (K1 * B > kUpManySlabs && (M == 64 || M == 256)) ? kUpSmallRowsMany : kUpSmallRows;
+    if ((int64_t)N * std::min(K1, 4) <= (int64_t)2 * rows * K1) return 128;
     return M <= 192 ? 384 : 256;
 }
 // Up tiles are ordered by expert, then by groups of blocks, then by the
@@ -153,7 +163,7 @@ Dims dims_of(const unif_moe_config* c) {
 }
 
 // Rows of an up tile and of a down row tile.
-int up_rows(const Dims& m) { return m.bf16 ? up_tm(m.N, m.K1, m.M, m.d) : kF32T; }
+int up_rows(const Dims& m) { return m.bf16 ? up_tm(m.N, m.K1, m.B, m.M, m.d) : kF32T; }
 int down_rows(const Dims& m) { return m.bf16 ? down_shape(m.d).tm : kF32T; }
 
 // cfg without a pair capacity (workspaces sized for the worst case).

@@ -2,7 +2,8 @@
 slabs of a row more or less than a tile, against the oracle (MI355X only), by
 the protocols of tests/parity.py and tests/test_gpu_backward.py. With K = 4,
 calls of up to 960 tokens take 128-row tiles (d >= 256), larger ones 384 (256
-for blocks of 256 channels). b = 1 of 2 blocks by prefix: slab (0, 0) holds
+for blocks of 256 channels); more than 128 slabs of 64 or 256 channels take
+them up to 32 tokens per expert. b = 1 of 2 blocks by prefix: slab (0, 0) holds
 every token."""
 import pytest
 
@@ -28,3 +29,15 @@ def test_forward(n, M):
 def test_backward(n, M):
     run_backward(generate(get_config("vit_s16", n_tokens=n, d_model=256, block_width=M, **PREFIX)),
                  f"up tiles N={n} M={M}")
+
+
+# K = 16, 8 blocks: 136 slabs
+MANY = dict(n_experts=16, n_blocks=8, max_shared=8)
+
+
+@pytest.mark.parametrize("M", [64, 192, 256])
+@pytest.mark.parametrize("n", [544, 545])
+def test_many_slabs(n, M):
+    g = generate(get_config("vit_s16", n_tokens=n, d_model=256, block_width=M, **MANY))
+    run_case(g, f"up tiles, 136 slabs N={n} M={M}")
+    run_backward(g, f"up tiles, 136 slabs N={n} M={M}")
