@@ -322,13 +322,25 @@ int down_splits(const Dims& m) {
 
 // Whether the down-projection converts W_down to fp16 as it reads it instead of
 // taking the copy that the routing launch makes: a copy reads and writes every
-// weight once, the conversion costs vector instructions each time a row tile
-// reads one. The line lies at 256 tokens per expert (4 row tiles of 256 pairs
-// at 4 pairs per token). Padded BERT-large (241): routing 61 -> 29 us, down
-// 143 -> 167 us, the call 368 -> 353 us; padded BERT-base (455): 24 -> 22 us,
-// 60 -> 70 us, the call 160 -> 164 us.
-constexpr int kDownConvertTokens = 256;
-bool down_converts(const Dims& m) { return m.N <= kDownConvertTokens * m.K1; }
+// weight once, beside the decisions, which hide about 60 MB of it; the
+// conversion costs vector instructions each time a row tile reads a weight, so
+// it pays for few tokens (slots) per expert. Whole calls, copy -> conversion:
+//   tokens per expert       28           128          190          250
+//   d 384   8 MB         73.4 ->  72.1   82.5 ->  81.0   84.4 ->  84.7   95.3 ->  97.0 us
+//   d 512  35 MB          172 ->   173    293 ->   296    328 ->   334    302 ->   317
+//   d 768  42 MB          114 ->   117    159 ->   167    170 ->   176    200 ->   206
+//   d 768  80 MB          170 ->   166    271 ->   267    307 ->   310    342 ->   349
+//   d 1152 120 MB         187 ->   170    317 ->   305    360 ->   346    414 ->   407
+//   d 1024 142 MB         237 ->   209    372 ->   357    435 ->   428    469 ->   473
+// Copies of less than 16 MB differ by 2% at most either way. Half padded calls
+// (whose slots are counted) gain at 241 slots per expert too: padded BERT-large
+// (142 MB) 357 -> 342 us.
+constexpr size_t kDownCopySmall = (size_t)16 << 20, kDownCopyHidden = (size_t)64 << 20, kDownCopyLarge = (size_t)96 << 20;
+bool down_converts(const Dims& m) {
+    const size_t bytes = (size_t)m.K1 * m.d * m.H * 2;
+    const int tokens = (bytes < kDownCopySmall || bytes >= kDownCopyLarge) ? 256 : (bytes >= kDownCopyHidden ? 128 : 0);
+    return m.N <= tokens * m.K1;
+}
 
 // The routing record's region is reserved whether or not the caller passes
 // its own record, so every other offset is the same for both kinds of call
