@@ -182,6 +182,11 @@ int32_t unif_moe_layer_forward_workspace_size(const unif_moe_config* cfg, size_t
  *          linear layer)
  *   Y      [N, d] (cfg->dtype), written for every row (zero for padded rows)
  *   routing_out  optional record (NULL: kept inside the workspace)
+ * Expert weights that are not finite: in fp32 layers a block's Inf or NaN
+ * reaches the outputs of the tokens that run the block and no others. bf16
+ * layers multiply the blocks of 32 pairs of an expert together, with zeros for
+ * the pairs that lack one, so an Inf or NaN in W_down can make those outputs
+ * NaN too.
  * Precision of the bf16 path: the up-projection multiplies bf16 values
  * (exact products, fp32 accumulation); the GELU activations are rounded to
  * fp16 and multiplied with W_down in fp16 (a copy made in the workspace at

@@ -87,6 +87,8 @@ __device__ __forceinline__ f32x4 f32_load4(const float* row, int i, int n) {
     return v;
 }
 
+__device__ __forceinline__ bool f32_finite(float v) { return (__float_as_uint(v) & 0x7f800000u) != 0x7f800000u; }
+
 // Which 4 values of a stage this thread loads as its piece u (0 or 1): for an
 // operand of k rows, row f32_row(u) and k f32_k(); for index rows, k f32_kr(u)
 // and index f32_idx().
@@ -265,10 +267,30 @@ __global__ __launch_bounds__(256) void f32_down_kernel(F32Params p) {
             });
         }
         const int col = n0 + f32_out_col();
+        uint32_t again = 0;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int r = f32_out_row(v);
-            if (r < nrows && col < p.d) p.part[(size_t)(p0 + r) * p.d + col] = acc[v];
+            if (r < nrows && col < p.d) {
+                p.part[(size_t)(p0 + r) * p.d + col] = acc[v];
+                if (!f32_finite(acc[v]) && rmask[r] != all) again |= 1u << v;
+            }
+        }
+        // A row that lacks one of the tile's blocks has zeros there, and zero
+        // times a weight that is not finite is a NaN. Such a block must not
+        // reach the rows that do not run it: their sums are formed again from
+        // their own blocks alone.
+        while (again) {
+            const int r = f32_out_row(__builtin_ctz(again));
+            again &= again - 1;
+            const float* a = src + (size_t)(p0 + r) * p.H;
+            const float* w = DX ? p.Wup + (size_t)e * p.H * p.d + col : p.Wdown + ((size_t)e * p.d + col) * p.H;
+            float sum = 0.f;
+            for (uint64_t m = rmask[r]; m; m &= m - 1) {
+                const int h0 = __builtin_ctzll(m) * p.M;
+                for (int h = h0; h < h0 + p.M; ++h) sum = fmaf(a[h], w[DX ? (size_t)h * p.d : (size_t)h], sum);
+            }
+            p.part[(size_t)(p0 + r) * p.d + col] = sum;
         }
     }
 }

@@ -2,11 +2,12 @@
 channels or columns, 32 k), against the oracle by the protocols of
 tests/parity.py and tests/test_gpu_backward.py (MI355X only), and the
 workspace-free forward of a layer whose activations do not fit its scratch,
-which runs on the per-pair kernel."""
+which runs on the per-pair kernel. A weight that is not finite reaches the
+tokens that run its block and no others."""
 import numpy as np
 import pytest
 
-from synth import generate, get_config, layer_config
+from synth import generate, get_config, layer_config, upstream_grad
 from tests import parity
 from tests.test_gpu_backward import run_backward
 from tests.test_gpu_parity import run_case
@@ -69,3 +70,55 @@ def test_static_forward_past_its_activations():
     print(f"[gpu] fp32 static forward: {err:.1e} x RMS from the workspace forward", flush=True)
     assert err <= parity.KERNEL_TOL["f32"]
     assert np.isfinite(err)
+
+
+def _spoiled(blocks_of):
+    """The layer of the test above with an Inf and a NaN in W_down (or W_up,
+    for the backward) of two blocks of two experts, and which tokens run one."""
+    from paper_2608_10392_amd.layer import DeviceLayer
+    g = _generate(3000, 32, 8, 8, 192)
+    bad = {k: g[k].copy() for k in ("W_up", "W_down")}
+    bad[blocks_of] = bad[blocks_of].copy()
+    for e, c, v in ((0, 2, np.inf), (3, 5, np.nan)):
+        if blocks_of == "W_down":
+            bad["W_down"][e, 7, c * 192 + 100] = v
+        else:
+            bad["W_up"][e, c * 192 + 100, 7] = v
+    cfg = layer_config(g["cfg"])
+    dev = [DeviceLayer(cfg, g["X"], g["valid"], g["W_router"], g["prototypes"], w["W_up"], w["W_down"])
+           for w in (g, bad)]
+    dev[0].forward()
+    r = dev[0].routing_numpy()
+    shared = (r["shared_mask"][:, None] >> np.arange(8, dtype=np.uint64)) & np.uint64(1) == 1
+    chosen = np.array([3 in r["expert_ids"][t, :r["n_res"][t]] for t in range(3000)])
+    uses = shared[:, 2] | (chosen & ~shared[:, 5])
+    assert 100 < uses.sum() < 2900
+    return g, cfg, dev, uses
+
+
+def test_weights_that_are_not_finite_stay_in_their_block():
+    """Tokens that do not run a block get the output they would get without
+    its Inf or NaN, whichever kernel runs; those that do get one that is not
+    finite."""
+    from paper_2608_10392_amd import _lib
+    g, cfg, (clean, bad), uses = _spoiled("W_down")
+    ref = clean.Y.cpu().numpy().astype(np.float64)
+    rms = np.sqrt(np.mean(ref ** 2))
+    bad.forward()
+    S = torch.empty_like(bad.Y)
+    _lib.layer_forward_static(cfg, bad.X, bad.valid, bad.W_router, bad.prototypes, bad.W_up, bad.W_down, S)
+    torch.cuda.synchronize()
+    for Y in (bad.Y, S):
+        y = Y.cpu().numpy().astype(np.float64)
+        assert not np.any(np.isfinite(y[uses, 7]))
+        assert np.all(np.isfinite(y[~uses]))
+        assert np.abs(y[~uses] - ref[~uses]).max() <= parity.KERNEL_TOL["f32"] * rms
+
+
+def test_gradients_past_weights_that_are_not_finite():
+    g, cfg, (clean, bad), uses = _spoiled("W_up")
+    dY = upstream_grad(g)
+    ref, got = (d.backward(dY)["dX"].cpu().numpy().astype(np.float64) for d in (clean, bad))
+    assert not np.any(np.isfinite(got[uses, 7]))
+    assert np.all(np.isfinite(got[~uses]))
+    assert np.abs(got[~uses] - ref[~uses]).max() <= parity.KERNEL_TOL["f32"] * np.abs(ref).max()
