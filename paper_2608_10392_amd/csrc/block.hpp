@@ -301,7 +301,7 @@ template <bool BF16>
 __global__ __launch_bounds__(256) void combine_block_flat_kernel(BlockCombineParams c) {
     constexpr int E = BF16 ? 4 : 1;
     const int nch = c.d / E;
-    const size_t item = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const size_t item = flat_block() * blockDim.x + threadIdx.x;
     if (item >= (size_t)c.N * nch) return;
     const int t = (int)(item / nch), ch = (int)(item - (size_t)t * nch);
     float z[E];
@@ -337,16 +337,15 @@ __device__ __forceinline__ double block_sum_f64(double v, double* lds) {
     return s;
 }
 
-// Post-LN: one workgroup per token, about one chunk per thread; z stays in
-// LDS (d floats; each lane reads back only what it wrote) for the LayerNorm.
-// (One wave per token left two waves per SIMD on the padded BERT-large batch,
-// each with its chunks one after another.)
+// Post-LN: one workgroup per token, about one chunk per thread; z stays in LDS (d floats; each lane reads back only
+// what it wrote) for the LayerNorm.
 template <bool BF16>
 __global__ __launch_bounds__(256) void combine_block_post_kernel(BlockCombineParams c) {
     constexpr int E = Chunk<BF16>::E;
     extern __shared__ __attribute__((aligned(16))) float zrow[];
     double* sums = reinterpret_cast<double*>(zrow + ((c.d + 1) & ~1));   // past one wave
-    const int t = blockIdx.x, T = blockDim.x;
+    if (flat_block() >= (size_t)c.N) return;
+    const int t = (int)flat_block(), T = blockDim.x;
     const int nch = c.d / E;
     char* yr = static_cast<char*>(c.Y) + (size_t)t * c.d * (BF16 ? 2 : 4);
     if (ld_uniform(c.totals + 5) != 0) {

@@ -191,6 +191,9 @@ __device__ __forceinline__ uint64_t lanes_below() {
     return (lane_id() == 0) ? 0ull : (~0ull >> (kWave - lane_id()));
 }
 
+// This workgroup's number in a grid of one or two dimensions.
+__device__ __forceinline__ size_t flat_block() { return (size_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
 __host__ __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // Sort key of a B-bit block mask: its top kb bits (kb <= 16), replaced by

@@ -679,7 +679,8 @@ __global__ __launch_bounds__(kSplitWaves * 64) void route_split_k_kernel(RoutePa
     if (route_copy_role(p)) return;
     extern __shared__ __attribute__((aligned(16))) float lds_route[];
     const int ls = p.lstride, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int tile = blockIdx.x, part = kTileTok * ls;
+    const int tile = NCT > 0 ? (int)blockIdx.x : (int)flat_block(), part = kTileTok * ls;
+    if (NCT == 0 && flat_block() >= (size_t)(p.N + kTileTok - 1) / kTileTok) return;
     if constexpr (NCT > 0) split_k_logits_bf16<NCT>(p, lds_route + wave * part, tile * kTileTok, wave);
     else split_k_logits_f32(p, lds_route + wave * part, tile * kTileTok, wave);
     __syncthreads();

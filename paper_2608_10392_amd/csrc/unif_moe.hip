@@ -174,6 +174,13 @@ unif_moe_config worst_case(unif_moe_config c) {
 
 // Counters per tile of the permutation: rows per slab, then pairs per expert.
 size_t tile_counters(const Dims& m) { return (size_t)m.nslab + m.K1; }
+// A grid of at least `blocks` workgroups, numbered by flat_block(): the threads
+// of a grid's x dimension are limited to 2^32 - 1.
+dim3 flat_grid(size_t blocks) {
+    const size_t x = (size_t)1 << 22;
+    return blocks <= x ? dim3((unsigned)blocks) : dim3((unsigned)x, (unsigned)((blocks + x - 1) / x));
+}
+
 // Routing LDS: logit rows of 64 tokens per wave (the wide kernel's share the
 // space with its stages of router rows), then the bit matrices of the tiles a
 // workgroup decides.
@@ -547,7 +554,7 @@ int32_t launch_route(const Dims& m, RouteParams rp, const float* Wr, const float
     const int grid = wide ? ceil_div(ntiles, kWideWaves) : ntiles;
     if (allow_lds(kern, lds) != UNIF_OK) return UNIF_EDEVICE;
     rp.cvt_blocks = copy_blocks(256);
-    kern<<<grid + rp.cvt_blocks, 256, lds, st>>>(rp);
+    kern<<<m.bf16 ? dim3((unsigned)(grid + rp.cvt_blocks)) : flat_grid((size_t)grid), 256, lds, st>>>(rp);
     UNIF_LAUNCH_CHECK();
     return UNIF_OK;
 }
@@ -960,24 +967,26 @@ int32_t forward_impl(const unif_moe_config* cfg, const unif_moe_block* blk, cons
         bc.totals = totals;
         if (!bc.post) {
             const int nch = m.bf16 ? m.d / 4 : m.d;
-            const unsigned g = (unsigned)(((size_t)m.N * nch + 255) / 256);
+            const dim3 g = flat_grid(((size_t)m.N * nch + 255) / 256);
             if (m.bf16) combine_block_flat_kernel<true><<<g, 256, 0, st>>>(bc);
             else combine_block_flat_kernel<false><<<g, 256, 0, st>>>(bc);
         } else {
             // One fp32 row in LDS; one chunk per thread up to 256 threads.
             // Rows that fill LDS leave no room for the waves' sums: one wave.
-            unsigned threads = (unsigned)std::min(256, ceil_div(m.bf16 ? m.d / 8 : m.d, 64) * 64);
+            const int chunks = m.bf16 ? m.d / 8 : m.d;
+            unsigned threads = (unsigned)std::min(256, ceil_div(chunks, 64) * 64);
             size_t lds = (size_t)((m.d + 1) & ~1) * sizeof(float) + (threads / 64) * sizeof(double);
             if (lds > kLdsLimit) {
                 threads = 64;
                 lds = (size_t)m.d * sizeof(float);
             }
+            const dim3 g = flat_grid((size_t)m.N);
             if (m.bf16) {
                 if (allow_lds(combine_block_post_kernel<true>, lds) != UNIF_OK) return UNIF_EDEVICE;
-                combine_block_post_kernel<true><<<(unsigned)m.N, threads, lds, st>>>(bc);
+                combine_block_post_kernel<true><<<g, threads, lds, st>>>(bc);
             } else {
                 if (allow_lds(combine_block_post_kernel<false>, lds) != UNIF_OK) return UNIF_EDEVICE;
-                combine_block_post_kernel<false><<<(unsigned)m.N, threads, lds, st>>>(bc);
+                combine_block_post_kernel<false><<<g, threads, lds, st>>>(bc);
             }
         }
         UNIF_LAUNCH_CHECK();
