@@ -337,7 +337,8 @@ __device__ __forceinline__ double block_sum_f64(double v, double* lds) {
     return s;
 }
 
-// Post-LN: one workgroup per token, about one chunk per thread; z stays in LDS (d floats; each lane reads back only
+// Post-LN: one workgroup per token, about one chunk per thread or one wave in
+// all (kPostWaveTokens); z stays in LDS (d floats; each lane reads back only
 // what it wrote) for the LayerNorm.
 template <bool BF16>
 __global__ __launch_bounds__(256) void combine_block_post_kernel(BlockCombineParams c) {

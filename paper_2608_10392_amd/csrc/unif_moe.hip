@@ -181,6 +181,15 @@ dim3 flat_grid(size_t blocks) {
     return blocks <= x ? dim3((unsigned)blocks) : dim3((unsigned)x, (unsigned)((blocks + x - 1) / x));
 }
 
+// The post-LN merge takes one wave per token from this many tokens (32 waves
+// per compute unit) of rows of at most kPostWaveChunks chunks, else a workgroup
+// of a thread per chunk, up to four waves, which wait for each other twice.
+// bf16, d = 1152: 1,000 tokens 113 us with a workgroup and 121 with a wave (the
+// whole block), 8,192 tokens 177 and 172, 30,000 tokens 516 and 495; fp32, d =
+// 384: 4,096 tokens 148 and 151, 30,000 tokens 638 and 604; fp32, d = 1024
+// (1,024 chunks of one value): 8,192 tokens 196 and 207, 30,000 tokens 591 and 594.
+constexpr int kPostWaveTokens = 8192, kPostWaveChunks = 512;
+
 // Routing LDS: logit rows of 64 tokens per wave (the wide kernel's share the
 // space with its stages of router rows), then the bit matrices of the tiles a
 // workgroup decides.
@@ -971,12 +980,13 @@ int32_t forward_impl(const unif_moe_config* cfg, const unif_moe_block* blk, cons
             if (m.bf16) combine_block_flat_kernel<true><<<g, 256, 0, st>>>(bc);
             else combine_block_flat_kernel<false><<<g, 256, 0, st>>>(bc);
         } else {
-            // One fp32 row in LDS; one chunk per thread up to 256 threads.
+            // One fp32 row in LDS; one chunk per thread up to 256 threads, and
+            // one wave where the tokens alone fill the chip (kPostWaveTokens).
             // Rows that fill LDS leave no room for the waves' sums: one wave.
             const int chunks = m.bf16 ? m.d / 8 : m.d;
             unsigned threads = (unsigned)std::min(256, ceil_div(chunks, 64) * 64);
             size_t lds = (size_t)((m.d + 1) & ~1) * sizeof(float) + (threads / 64) * sizeof(double);
-            if (lds > kLdsLimit) {
+            if (lds > kLdsLimit || (m.N >= kPostWaveTokens && chunks <= kPostWaveChunks)) {
                 threads = 64;
                 lds = (size_t)m.d * sizeof(float);
             }

@@ -2,8 +2,9 @@
 shape changes: one wave, whole waves, several chunks per thread, and rows that
 leave no LDS for the waves' sums (one wave again), against the oracle by the
 protocol of tests/parity.py (MI355X only). More pathways than one batch of the
-merge holds, with biases and the residual. More than 2^32 threads take a grid
-of two dimensions."""
+merge holds, with biases and the residual. From 8,192 tokens of at most 512
+chunks a token takes one wave; more than 2^32 threads take a grid of two
+dimensions."""
 import pytest
 
 from synth import block_inputs, generate, get_config
@@ -32,6 +33,23 @@ def test_post_ln_rows(name):
                             mass_mode="topk", fixed_k=2 if wide else 9, **over))
     blk, X = block_inputs(g, "post", residual=True, eps=1e-6)
     run_block(g, blk, X, name)
+
+
+MANY = {
+    "f32_workgroup": ("tiny_f32", dict(n_tokens=8191, d_model=129)),
+    "f32_wave": ("tiny_f32", dict(n_tokens=8192, d_model=129)),
+    "f32_wave_512_chunks": ("tiny_f32", dict(n_tokens=8193, d_model=512)),
+    "f32_workgroup_513_chunks": ("tiny_f32", dict(n_tokens=8193, d_model=513)),
+    "bf16_wave": ("vit_s16", dict(n_tokens=8192, d_model=640)),
+}
+
+
+@pytest.mark.parametrize("name", list(MANY))
+def test_post_ln_many_tokens(name):
+    base, over = MANY[name]
+    g = generate(get_config(base, n_experts=3, n_blocks=2, block_width=64, max_shared=2, **over))
+    blk, X = block_inputs(g, "post", residual=True, eps=1e-6)
+    run_block(g, blk, X, name, n_sample=200)
 
 
 def test_post_ln_more_threads_than_a_grid_row():
