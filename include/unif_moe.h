@@ -166,9 +166,9 @@ int32_t unif_moe_route(const unif_moe_config* cfg, const void* X, const uint8_t*
  * activations, the per-expert rows, the pair and slab lists, the down-tile
  * tables) for that many pairs instead, which shrinks the workspace by about
  * N (K+1) / max_pairs for large layers. fp32 layers keep 4 H bytes of
- * activations per pair while these take at most 8 GiB; past that (and in
- * unif_moe_layer_forward_static where only that fits) the expert FFNs run
- * pair by pair with no such buffer, far slower. */
+ * activations per pair, but at most 1 GiB (or 256 N bytes, if that is more):
+ * layers that need more run the expert FFNs in passes over ranges of experts
+ * and, where one expert's do not fit, of its channels, with the same results. */
 int32_t unif_moe_layer_forward_workspace_size(const unif_moe_config* cfg, size_t* bytes);
 
 /* Forward pass of the layer: routing, token permutation, block-sparse expert
@@ -222,9 +222,9 @@ int32_t unif_moe_layer_forward(const unif_moe_config* cfg, const void* X, const 
  *   events[4] after the up-projection
  *   events[5] after the down-projection
  *   events[6] after the weighted merge
- * n_events must be 7. Where an fp32 layer runs pair by pair (see
- * unif_moe_layer_forward_workspace_size) events[4] and events[5] both follow
- * the per-pair FFN. Errors as unif_moe_layer_forward; UNIF_EINVAL for a NULL
+ * n_events must be 7. Where an fp32 layer runs in passes (see
+ * unif_moe_layer_forward_workspace_size) events[4] follows the last pass's
+ * up-projection. Errors as unif_moe_layer_forward; UNIF_EINVAL for a NULL
  * event array or n_events != 7. */
 int32_t unif_moe_layer_forward_profiled(const unif_moe_config* cfg, const void* X,
                                         const uint8_t* valid, const float* W_router,
@@ -301,8 +301,9 @@ int32_t unif_moe_block_forward(const unif_moe_config* cfg, const unif_moe_block*
  * the fp32 per-pair rows, which take dx per pair), and, for bf16 layers, a
  * second H-shaped buffer ((N(K+1) + 1) H bf16 values), a transposed copy of
  * W_down and 8 B N(K+1) bytes of per-block partial sums; for fp32 layers
- * 8 H N(K+1) bytes of activations and their gradients and
- * 8 B ceil(M / 64) N(K+1) bytes of partial sums. */
+ * 8 H N(K+1) bytes of activations and their gradients; their
+ * 8 B ceil(M / 64) N(K+1) bytes of partial sums lie where the forward keeps its
+ * activations, as far as they fit. */
 int32_t unif_moe_layer_backward_workspace_size(const unif_moe_config* cfg, size_t* bytes);
 
 /* Backward pass of the layer for a training step: the gradients of
@@ -329,7 +330,8 @@ int32_t unif_moe_layer_backward_workspace_size(const unif_moe_config* cfg, size_
  * d loss / da = w (dy V) GELU'(a) and w GELU(a), both rounded to bf16, which
  * feed dx = sum over blocks of (d loss / da) K and the weight gradients
  * (bf16 products, fp32 sums). fp32 layers run the same
- * products on the matrix cores in fp32 and require N <= 8,388,480. Requires d % 8 == 0 and what
+ * products on the matrix cores in fp32 and require N <= 8,388,480 and
+ * N K B + 64 (K+1) B <= INT32_MAX. Requires d % 8 == 0 and what
  * unif_moe_layer_forward requires; otherwise UNIF_EUNSUPPORTED. Errors as
  * unif_moe_layer_forward. */
 int32_t unif_moe_layer_backward(const unif_moe_config* cfg, const void* X, const uint8_t* valid,

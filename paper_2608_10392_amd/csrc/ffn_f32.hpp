@@ -31,9 +31,13 @@
 // is a last wave of workgroups (440 to 1,000 tiles over 1,024 places) and the
 // barrier and load latency of 12 to 50 stages per tile.
 //
-// pair_ffn_f32_kernel is the forward for layers whose activations would not
-// fit the workspace (see f32_gemm_path in unif_moe.hip): it holds one pair's
-// activations in LDS and needs no memory.
+// A forward's activations take a bounded part of the workspace: layers that
+// need more run in passes over ranges of experts, and where one expert's do not
+// fit, of its channels (F32Pass), with the same bits.
+//
+// pair_ffn_f32_kernel is the forward for layers that have no room for
+// activations and tables at all (the workspace-free forward): it holds one
+// pair's activations in LDS and needs no memory.
 #pragma once
 #include "common.hpp"
 
@@ -53,6 +57,17 @@ constexpr int kF32Gelu = 0, kF32Pre = 1, kF32Da = 2;
 __host__ __device__ __forceinline__ int f32_chunks(int M) { return ceil_div(M, kF32T); }
 __host__ __device__ __forceinline__ int f32_partials(int B, int M) { return 2 * B * f32_chunks(M); }
 
+// What a pass of a forward covers: experts [e0, e0 + ne) and channels [h0, h0 +
+// hw) (cut at M) of blocks [c0, c0 + nc). The activations of the experts' pairs
+// take `stride` floats each, from the first of them on, channel h of block c at
+// (c - c0) hw + h - h0. One pass over everything: channel h of block c of a pair
+// at c M + h. Parts of a block are multiples of 64 channels, so that the passes
+// of an expert take the stages that one pass would take, in its order.
+struct F32Pass {
+    int e0, ne, c0, nc, h0, hw, stride;
+    bool first;   // of its experts: the rows' sums start at zero
+};
+
 struct F32Params {
     int d, M, B, H;
     const float* X;
@@ -60,7 +75,8 @@ struct F32Params {
     const float* Wup;        // [K+1][H][d]
     const float* Wdown;      // [K+1][d][H]
     const float* b_up;       // [K+1][H] biases added before the GELU, or null
-    float* act;              // [pairs][H], active blocks only
+    F32Pass ps;              // what act holds (backward: everything)
+    float* act;              // [pairs of the pass][ps.stride], active blocks only
     float* da;               // [pairs][H], active blocks only (backward)
     float* dcp;              // [pairs][f32_partials] (backward)
     const float* pw;         // pair weights (backward)
@@ -73,7 +89,9 @@ struct F32Params {
     const int4* rt_info;     // down row tiles, as for bf16 layers
     const uint64_t* rt_masks;
     const uint64_t* pair_mask;
-    const int* slab_off;     // weight gradients
+    const int* seg_off;      // [K+2] first pair of each expert
+    const int* down_tile_off;   // [K+2] first down row tile of each expert
+    const int* slab_off;     // first row of each slab in the lists, a multiple of a tile's rows
     const int* slab_count;
     float* dW;
 };
@@ -101,12 +119,12 @@ __device__ __forceinline__ int f32_idx() { return ((int)threadIdx.x & 15) * 4; }
 // the tile. fa(s, u), fb(s, u) load this thread's piece u of stage s; AROWS /
 // BROWS: the operand is staged as rows of k (else rows of its index). Lane l
 // gets column l % 32 and rows 8 j + 4 (l / 32) + i in element 4 j + i. The
-// caller has passed a barrier since the last use of lds.
+// caller has passed a barrier since the last use of lds. The sum goes on from
+// acc.
 template <bool AROWS, bool BROWS, class FA, class FB>
-__device__ __forceinline__ f32x16 f32_tile(float* lds, int nst, FA fa, FB fb) {
+__device__ __forceinline__ f32x16 f32_tile(float* lds, int nst, FA fa, FB fb, f32x16 acc = f32x16{}) {
     const int lane = lane_id(), wave = (int)threadIdx.x >> 6, lr = lane & 31, lh = lane >> 5;
     const int ra = (wave >> 1) * 32 + lr, rb = (wave & 1) * 32 + lr;
-    f32x16 acc = f32x16{};
     if (nst <= 0) return acc;
     f32x4 va[2], vb[2];
     auto load = [&](int s) {
@@ -161,17 +179,22 @@ template <int MODE>
 __global__ __launch_bounds__(256) void f32_up_kernel(F32Params p) {
     __shared__ __attribute__((aligned(16))) float lds[kF32LdsFloats];
     __shared__ int tok[kF32T], pair[kF32T];
-    const int chunks = f32_chunks(p.M), n = p.totals[1] * chunks;
+    if (p.totals[1] == 0) return;   // no rows, or past the pair capacity: no tables
+    // Tiles are listed expert by expert, as many of each as its slabs fill.
+    const int t0 = p.slab_off[p.ps.e0 * p.B] / kF32T, t1 = min(p.totals[1], p.slab_off[(p.ps.e0 + p.ps.ne) * p.B] / kF32T);
+    const int hend = min(p.M, p.ps.h0 + p.ps.hw), pair0 = p.seg_off[p.ps.e0];
+    const int chunks = f32_chunks(hend - p.ps.h0), n = (t1 - t0) * chunks;
     for (int t = blockIdx.x; t < n; t += gridDim.x) {
-        const int tile = t / chunks, chunk = t - tile * chunks, h0 = chunk * kF32T;
+        const int tile = t0 + t / chunks, chunk = t % chunks, h0 = p.ps.h0 + chunk * kF32T;
         const int info = p.tile_info[tile], sl = info & 0xffff, nrows = info >> 16;
-        const int e = sl / p.B, c = sl - e * p.B, hw = p.M - h0;   // channels left in the block
+        const int e = sl / p.B, c = sl - e * p.B, hw = hend - h0;   // channels left
+        if (c < p.ps.c0 || c >= p.ps.c0 + p.ps.nc) continue;
         const int first = p.tile_rows[tile];
         __syncthreads();   // the last tile's products and rows are done with
         if (threadIdx.x < kF32T) {
             const bool in = (int)threadIdx.x < nrows;
             tok[threadIdx.x] = in ? p.slab_tok[first + threadIdx.x] : -1;
-            pair[threadIdx.x] = in ? p.slab_rows[first + threadIdx.x] : 0;
+            pair[threadIdx.x] = in ? p.slab_rows[first + threadIdx.x] : pair0;
         }
         __syncthreads();
         const float* xs = MODE == kF32Da ? p.dY : p.X;
@@ -201,7 +224,7 @@ __global__ __launch_bounds__(256) void f32_up_kernel(F32Params p) {
         for (int v = 0; v < 16; ++v) {
             const int r = f32_out_row(v);
             const bool ok = cok && r < nrows;
-            const size_t off = (size_t)pair[r] * p.H + ch;
+            const size_t off = (size_t)(pair[r] - pair0) * p.ps.stride + (size_t)(c - p.ps.c0) * p.ps.hw + (h0 - p.ps.h0) + col;
             if constexpr (MODE == kF32Gelu) {
                 if (ok) p.act[off] = gelu_erf(acc[v] + b1);
             } else if constexpr (MODE == kF32Pre) {
@@ -224,56 +247,68 @@ __global__ __launch_bounds__(256) void f32_up_kernel(F32Params p) {
     }
 }
 
-// DX: dx_pair = da K, else the expert rows act V.
-template <bool DX>
+// DX: dx_pair = da K, else the expert rows act V. FIRST: the first (or only)
+// pass of its experts; later ones go on from the rows' sums.
+template <bool DX, bool FIRST>
 __global__ __launch_bounds__(256) void f32_down_kernel(F32Params p) {
     __shared__ __attribute__((aligned(16))) float lds[kF32LdsFloats];
     __shared__ uint64_t rmask[kF32T];
     __shared__ int blocks[64];
-    const int ncol = ceil_div(p.d, kF32T), n = p.totals[4] * ncol;
-    const int spb = ceil_div(p.M, kF32K);   // stages per block
+    const int rt0 = p.down_tile_off[p.ps.e0], rt1 = min(p.totals[4], p.down_tile_off[p.ps.e0 + p.ps.ne]);
+    const int ncol = ceil_div(p.d, kF32T), n = (rt1 - rt0) * ncol, pair0 = p.seg_off[p.ps.e0];
+    const int hw = min(p.M - p.ps.h0, p.ps.hw);   // channels per block
+    const int spb = ceil_div(hw, kF32K);          // stages per block
+    const uint64_t in_pass = (p.ps.nc == 64 ? ~0ull : (1ull << p.ps.nc) - 1ull) << p.ps.c0;
     const float* src = DX ? p.da : p.act;
     for (int t = blockIdx.x; t < n; t += gridDim.x) {
-        const int rt = t / ncol, n0 = (t - rt * ncol) * kF32T;
+        const int rt = rt0 + t / ncol, n0 = (t % ncol) * kF32T;
         const int4 info = p.rt_info[rt];
         const int p0 = info.x, nrows = info.y, e = info.z;
-        const uint64_t all = p.rt_masks[(size_t)rt * (kF32T / 32 + 1) + kF32T / 32];
+        const uint64_t all = p.rt_masks[(size_t)rt * (kF32T / 32 + 1) + kF32T / 32] & in_pass;
+        if (!FIRST && all == 0) continue;
         __syncthreads();   // the last tile's products and rows are done with
         if (threadIdx.x < kF32T) {
-            rmask[threadIdx.x] = (int)threadIdx.x < nrows ? p.pair_mask[p0 + threadIdx.x] : 0ull;
+            rmask[threadIdx.x] = (int)threadIdx.x < nrows ? p.pair_mask[p0 + threadIdx.x] & in_pass : 0ull;
             if ((all >> threadIdx.x) & 1ull) blocks[__popcll(all & lanes_below())] = threadIdx.x;
         }
         __syncthreads();
         auto fa = [&](int s, int u) {
             const int q = s / spb, c = blocks[q], k = (s - q * spb) * kF32K + f32_k(), r = f32_row(u);
-            return ((rmask[r] >> c) & 1ull) ? f32_load4(src + (size_t)(p0 + r) * p.H + (size_t)c * p.M, k, p.M)
-                                            : f32x4{0.f, 0.f, 0.f, 0.f};
+            return ((rmask[r] >> c) & 1ull)
+                       ? f32_load4(src + (size_t)(p0 - pair0 + r) * p.ps.stride + (size_t)(c - p.ps.c0) * p.ps.hw, k, hw)
+                       : f32x4{0.f, 0.f, 0.f, 0.f};
         };
-        const int nst = __popcll(all) * spb;
-        f32x16 acc;
+        const int nst = __popcll(all) * spb, col = n0 + f32_out_col();
+        f32x16 acc = f32x16{};
+        if constexpr (!FIRST) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int r = f32_out_row(v);
+                if (r < nrows && col < p.d) acc[v] = p.part[(size_t)(p0 + r) * p.d + col];
+            }
+        }
         if constexpr (DX) {
-            const float* w = p.Wup + (size_t)e * p.H * p.d + n0;
+            const float* w = p.Wup + ((size_t)e * p.H + p.ps.h0) * p.d + n0;
             acc = f32_tile<true, false>(lds, nst, fa, [&](int s, int u) {
                 const int q = s / spb, k = (s - q * spb) * kF32K + f32_kr(u);
-                return k < p.M ? f32_load4(w + ((size_t)blocks[q] * p.M + k) * p.d, f32_idx(), p.d - n0)
-                               : f32x4{0.f, 0.f, 0.f, 0.f};
-            });
+                return k < hw ? f32_load4(w + ((size_t)blocks[q] * p.M + k) * p.d, f32_idx(), p.d - n0)
+                              : f32x4{0.f, 0.f, 0.f, 0.f};
+            }, acc);
         } else {
-            const float* w = p.Wdown + ((size_t)e * p.d + n0) * p.H;
+            const float* w = p.Wdown + ((size_t)e * p.d + n0) * p.H + p.ps.h0;
             acc = f32_tile<true, true>(lds, nst, fa, [&](int s, int u) {
                 const int q = s / spb, k = (s - q * spb) * kF32K + f32_k(), r = f32_row(u);
-                return n0 + r < p.d ? f32_load4(w + (size_t)r * p.H + (size_t)blocks[q] * p.M, k, p.M)
+                return n0 + r < p.d ? f32_load4(w + (size_t)r * p.H + (size_t)blocks[q] * p.M, k, hw)
                                     : f32x4{0.f, 0.f, 0.f, 0.f};
-            });
+            }, acc);
         }
-        const int col = n0 + f32_out_col();
         uint32_t again = 0;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int r = f32_out_row(v);
             if (r < nrows && col < p.d) {
-                p.part[(size_t)(p0 + r) * p.d + col] = acc[v];
                 if (!f32_finite(acc[v]) && rmask[r] != all) again |= 1u << v;
+                else p.part[(size_t)(p0 + r) * p.d + col] = acc[v];
             }
         }
         // A row that lacks one of the tile's blocks has zeros there, and zero
@@ -283,12 +318,16 @@ __global__ __launch_bounds__(256) void f32_down_kernel(F32Params p) {
         while (again) {
             const int r = f32_out_row(__builtin_ctz(again));
             again &= again - 1;
-            const float* a = src + (size_t)(p0 + r) * p.H;
-            const float* w = DX ? p.Wup + (size_t)e * p.H * p.d + col : p.Wdown + ((size_t)e * p.d + col) * p.H;
-            float sum = 0.f;
+            const float* a = src + (size_t)(p0 - pair0 + r) * p.ps.stride;
+            float sum = FIRST ? 0.f : p.part[(size_t)(p0 + r) * p.d + col];
             for (uint64_t m = rmask[r]; m; m &= m - 1) {
-                const int h0 = __builtin_ctzll(m) * p.M;
-                for (int h = h0; h < h0 + p.M; ++h) sum = fmaf(a[h], w[DX ? (size_t)h * p.d : (size_t)h], sum);
+                const int c = __builtin_ctzll(m);
+                for (int h = 0; h < hw; ++h) {
+                    const size_t ch = (size_t)c * p.M + p.ps.h0 + h;
+                    sum = fmaf(a[(size_t)(c - p.ps.c0) * p.ps.hw + h],
+                               DX ? p.Wup[((size_t)e * p.H + ch) * p.d + col] : p.Wdown[((size_t)e * p.d + col) * p.H + ch],
+                               sum);
+                }
             }
             p.part[(size_t)(p0 + r) * p.d + col] = sum;
         }

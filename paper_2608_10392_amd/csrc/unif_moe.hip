@@ -17,7 +17,7 @@
 //                    up tile table
 //   down_tables      down row tiles and their block-mask unions
 //   up, down         block-sparse MFMA grouped GEMMs, bf16 or fp32
-//                    (fp32 layers past f32_gemm_path's bound: pair_ffn_f32,
+//                    (workspace-free fp32 forwards without the room: pair_ffn_f32,
 //                    with no tables)
 //   combine          weighted merge in fixed order
 // The block forward adds a LayerNorm pass before routing (pre-LN) and
@@ -123,19 +123,65 @@ struct Dims {
     int N, d, K, B, M, H, K1, NL, NLP, lstride, key_bits, nslab, nbin;
     size_t pcap;   // (token, expert) pairs the forward's workspace holds (cfg max_pairs, else N (K+1))
     bool bf16;
-    bool tables;   // slab lists and tile tables are built (all layers but fp32 ones on pair_ffn_f32)
+    bool tables;   // slab lists and tile tables are built (all layers but fp32 ones on pair_ffn_f32_kernel)
     size_t elem;
     float tau, one_minus_2tau;
 };
 
-// fp32 forwards run on the matrix cores when the activations of every pair of
-// the worst case (or of max_pairs) take at most 8 GiB of workspace; past that
-// the per-pair kernel, which holds one pair's activations in LDS, keeps the
-// workspace what it was (a 1,576-token DeiT-S layer needs 68 MB; the limit is
-// a bound on what a forward may add to a caller's memory, not a crossover:
-// the GEMMs are over 50 times faster at any size).
-constexpr size_t kF32ActBytes = (size_t)8 << 30;
-bool f32_gemm_path(const Dims& m) { return m.pcap * (size_t)m.H * sizeof(float) <= kF32ActBytes; }
+// fp32 forwards keep the activations of every pair of the worst case (or of
+// max_pairs) in at most this much workspace, or 64 channels of one expert's
+// pairs if that is more; layers that need more run in passes (F32Pass). It
+// bounds what the matrix cores' path adds to a caller's memory.
+constexpr size_t kF32ActBytes = (size_t)1 << 30;
+// Slab rows are numbered in 32 bits, each slab padded to whole tiles.
+bool f32_rows_fit(const Dims& m) {
+    return (int64_t)m.N * m.K * m.B + (int64_t)kF32T * m.nslab <= INT32_MAX;
+}
+// The most pairs that ne experts can have.
+size_t f32_rows(const Dims& m, int ne) { return std::min(m.pcap, (size_t)m.N * (size_t)ne); }
+// The first pass of an fp32 forward: everything; or as many experts as fit; or
+// one expert and as many blocks, or as much of a block, as fit.
+F32Pass f32_first(const Dims& m) {
+    const size_t fit = kF32ActBytes / sizeof(float);
+    F32Pass w{0, m.K1, 0, m.B, 0, m.M, m.H, true};
+    const size_t one = std::max<size_t>(f32_rows(m, 1), 1);
+    if (f32_rows(m, m.K1) * (size_t)m.H <= fit) return w;
+    if (one * (size_t)m.H <= fit) {
+        const int most = (int)std::min<size_t>(m.K1, fit / (one * (size_t)m.H));
+        w.ne = ceil_div(m.K1, ceil_div(m.K1, most));
+        return w;
+    }
+    w.ne = 1;
+    const int most = (int)(fit / one);   // channels per pair, fewer than H
+    if (most >= m.M) {
+        w.nc = ceil_div(m.B, ceil_div(m.B, most / m.M));
+    } else {
+        w.nc = 1;
+        w.hw = std::min(m.M, ceil_div(ceil_div(m.M, ceil_div(m.M, std::max(1, most / kF32T) * kF32T)), kF32T) * kF32T);
+    }
+    w.stride = w.nc * w.hw;
+    return w;
+}
+// The pass after w; false if that was the last.
+bool f32_next(const Dims& m, F32Pass& w) {
+    w.first = false;
+    if (w.h0 + w.hw < m.M) {
+        w.h0 += w.hw;
+        return true;
+    }
+    w.h0 = 0;
+    w.c0 += w.nc;
+    if (w.c0 < m.B) {
+        w.nc = std::min(w.nc, m.B - w.c0);
+        return true;
+    }
+    const F32Pass f = f32_first(m);
+    const int e0 = w.e0 + w.ne;
+    w = f;
+    w.e0 = e0;
+    w.ne = std::min(w.ne, m.K1 - e0);
+    return e0 < m.K1;
+}
 
 Dims dims_of(const unif_moe_config* c) {
     Dims m;
@@ -155,7 +201,7 @@ Dims dims_of(const unif_moe_config* c) {
     const size_t worst = (size_t)m.N * (size_t)m.K1;
     m.pcap = (c->max_pairs > 0 && (size_t)c->max_pairs < worst) ? (size_t)c->max_pairs : worst;
     m.bf16 = c->dtype == UNIF_BF16;
-    m.tables = m.bf16 || f32_gemm_path(m);
+    m.tables = m.bf16 || f32_rows_fit(m);
     m.elem = m.bf16 ? 2 : 4;
     m.tau = std::isnan(c->tau) ? (float)((double)(m.B - 1) / ((double)m.B * (double)m.B)) : c->tau;
     m.one_minus_2tau = 1.0f - 2.0f * m.tau;
@@ -312,7 +358,7 @@ struct FwdPlan {
     size_t bin_count, slab_count, exp_total, totals, queues, zero_page, work;
     size_t bin_cursor, seg_off, slab_off, down_tile_off, tile_cnt, max_row_tiles, rt_info, rt_masks;
     size_t pair_token, pair_mask, pair_expert, pair_of, pair_rank, slab_rows, slab_tok, up_tile_info, up_tile_rows, hbuf, part;
-    size_t act;     // fp32 activations of each pair (fp32 layers with tables)
+    size_t act, act_bytes;   // fp32 activations of each pair (fp32 layers with tables)
     size_t xn;      // LN(X), the FFN input of a pre-LN block
     size_t wdown16; // fp16 copy of W_down (bf16 layers)
     size_t down_slices; // [kXcds + 1] down tiles per XCD queue
@@ -405,7 +451,9 @@ FwdPlan plan_forward(const Dims& m, size_t xn_bytes = 0) {
     p.slab_tok = cv.take(m.tables ? 4 * up_tiles * tm : 0);
     p.up_tile_info = cv.take(m.tables ? 4 * up_tiles : 0);
     p.up_tile_rows = cv.take(m.tables ? 4 * up_tiles : 0);
-    p.act = cv.take(!m.bf16 && m.tables ? pmax * (size_t)m.H * sizeof(float) : 0);
+    const F32Pass fp = f32_first(m);
+    p.act_bytes = !m.bf16 && m.tables ? f32_rows(m, fp.ne) * (size_t)fp.stride * sizeof(float) : 0;
+    p.act = cv.take(p.act_bytes);
     p.hbuf = cv.take(m.bf16 ? (pmax + 1) * (size_t)m.H * 2 : 0);  // fp16, + the sink row
     p.part = cv.take((pmax + 1) * (size_t)m.d * sizeof(float) * down_splits(m));   // fp32, + the sink row, per part
     p.xn = cv.take(xn_bytes);
@@ -674,6 +722,9 @@ F32Params f32_params(const Dims& m, const FwdPlan& plan, char* ws, const void* X
     f.X = static_cast<const float*>(X);
     f.Wup = static_cast<const float*>(W_up);
     f.Wdown = static_cast<const float*>(W_down);
+    f.ps = f32_first(m);
+    f.seg_off = reinterpret_cast<const int*>(ws + plan.seg_off);
+    f.down_tile_off = reinterpret_cast<const int*>(ws + plan.down_tile_off);
     f.act = reinterpret_cast<float*>(ws + plan.act);
     f.part = reinterpret_cast<float*>(ws + plan.part);
     f.slab_rows = reinterpret_cast<const int*>(ws + plan.slab_rows);
@@ -691,8 +742,8 @@ F32Params f32_params(const Dims& m, const FwdPlan& plan, char* ws, const void* X
 unsigned f32_grid(int cus) { return (unsigned)cus * 4; }
 
 // kTables: stop after the permutation (the backward's front part).
-// kNoTables: the forward of an fp32 layer on the per-pair kernel, whatever
-// f32_gemm_path says (it needs the least workspace).
+// kNoTables: the forward of an fp32 layer on the per-pair kernel (it needs the
+// least workspace).
 enum class Run { kForward, kTables, kNoTables };
 
 Dims dims_for(const unif_moe_config* c, Run run) {
@@ -920,11 +971,17 @@ int32_t forward_impl(const unif_moe_config* cfg, const unif_moe_block* blk, cons
         if (m.tables) {
             F32Params fp = f32_params(m, plan, ws, Xf, W_up, W_down);
             fp.b_up = blk != nullptr ? blk->b_up : nullptr;
-            f32_up_kernel<kF32Gelu><<<f32_grid(cus), 256, 0, st>>>(fp);
-            UNIF_LAUNCH_CHECK();
-            UNIF_MARK(4);
-            f32_down_kernel<false><<<f32_grid(cus), 256, 0, st>>>(fp);
-            UNIF_LAUNCH_CHECK();
+            for (bool more = true; more;) {
+                f32_up_kernel<kF32Gelu><<<f32_grid(cus), 256, 0, st>>>(fp);
+                UNIF_LAUNCH_CHECK();
+                F32Pass next = fp.ps;
+                more = f32_next(m, next);
+                if (!more) UNIF_MARK(4);
+                if (fp.ps.first) f32_down_kernel<false, true><<<f32_grid(cus), 256, 0, st>>>(fp);
+                else f32_down_kernel<false, false><<<f32_grid(cus), 256, 0, st>>>(fp);
+                UNIF_LAUNCH_CHECK();
+                fp.ps = next;
+            }
             UNIF_MARK(5);
         } else {
         PairF32Params fp;
@@ -1097,19 +1154,31 @@ int wgrad_ntn(const Dims& m) { return m.d % 256 == 0 ? m.d / 256 : m.d / 128; }
 
 BwdPlan plan_backward(const Dims& m) {
     BwdPlan b;
-    b.fwd = plan_forward(m).total;   // includes its own 256 bytes of alignment slack
+    const FwdPlan f = plan_forward(m);
+    b.fwd = f.total;   // includes its own 256 bytes of alignment slack
     const size_t pmax = (size_t)m.N * m.K1;
     Carver cv;
     cv.cur = b.fwd;
+    // fp32: what fits of the small regions lies where the forward keeps its
+    // activations (the backward has its own, of all channels).
+    Carver in;
+    in.cur = f.act;
+    auto small = [&](size_t bytes) {
+        Carver t = in;
+        const size_t o = t.take(bytes);
+        if (t.cur > f.act + f.act_bytes) return cv.take(bytes);
+        in = t;
+        return o;
+    };
     b.act = cv.take(m.bf16 ? 0 : pmax * m.H * sizeof(float));
     b.da = cv.take(m.bf16 ? 0 : pmax * m.H * sizeof(float));
     b.gbuf = cv.take(m.bf16 ? (pmax + 1) * (size_t)m.H * 2 : 0);   // + the sink row
     b.wdnT = cv.take(m.bf16 ? (size_t)m.K1 * m.d * m.H * 2 : 0);
-    b.dcp = cv.take(m.bf16 ? (pmax + 1) * m.B * 2 * sizeof(float) : pmax * f32_partials(m.B, m.M) * sizeof(float));
-    b.dcoef = cv.take(pmax * sizeof(float));
-    b.pw = cv.take(pmax * sizeof(float));
-    b.dz = cv.take((size_t)m.N * m.K1 * sizeof(float));
-    b.rpart = cv.take((size_t)kRouterChunks * m.K1 * m.d * sizeof(float));
+    b.dcp = small(m.bf16 ? (pmax + 1) * m.B * 2 * sizeof(float) : pmax * f32_partials(m.B, m.M) * sizeof(float));
+    b.dcoef = small(pmax * sizeof(float));
+    b.pw = small(pmax * sizeof(float));
+    b.dz = small((size_t)m.N * m.K1 * sizeof(float));
+    b.rpart = small((size_t)kRouterChunks * m.K1 * m.d * sizeof(float));
     // The weight gradients' units; their partial sums take the place of the
     // per-pair rows, which are done with by then.
     b.slots = m.bf16 ? (int)std::min<size_t>(pmax / (2 * m.M), (size_t)1 << 16) : 0;   // for each of the two gradients
@@ -1127,7 +1196,8 @@ int32_t check_backward_shape(const unif_moe_config* c) {
     if (s != UNIF_OK) return s;
     s = check_forward_shape(c);
     if (s != UNIF_OK) return s;
-    if (c->dtype == UNIF_F32 && c->n_tokens > kF32BackwardMaxTokens) return UNIF_EUNSUPPORTED;
+    if (c->dtype == UNIF_F32 && (c->n_tokens > kF32BackwardMaxTokens || !f32_rows_fit(dims_of(c))))
+        return UNIF_EUNSUPPORTED;
     // the per-token and router-gradient kernels take 4 and 8 columns at a time
     if (c->d_model % 8 != 0) return UNIF_EUNSUPPORTED;
     return UNIF_OK;
@@ -1330,6 +1400,7 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
     } else {
         // 2. the same products in fp32: a = x K^T, dy V, dx_pair = da K
         f = f32_params(m, fp, ws, X, W_up, W_down);
+        f.ps = F32Pass{0, m.K1, 0, m.B, 0, m.M, m.H, true};
         f.dY = static_cast<const float*>(dY);
         f.act = reinterpret_cast<float*>(ws + bp.act);
         f.da = reinterpret_cast<float*>(ws + bp.da);
@@ -1339,7 +1410,7 @@ int32_t unif_moe_layer_backward(const unif_moe_config* cfg_in, const void* X, co
         f32_up_kernel<kF32Pre><<<f32_grid(cus), 256, 0, st>>>(f);
         f32_up_kernel<kF32Da><<<f32_grid(cus), 256, 0, st>>>(f);
         bwd_dcoef_sum_kernel<<<(unsigned)cus * 4, 256, 0, st>>>(p, dcp, 2 * f32_chunks(m.M));
-        f32_down_kernel<true><<<f32_grid(cus), 256, 0, st>>>(f);
+        f32_down_kernel<true, true><<<f32_grid(cus), 256, 0, st>>>(f);
         UNIF_LAUNCH_CHECK();
     }
     // 5. per token: dX and the router-logit gradients; the router's weight gradient

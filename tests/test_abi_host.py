@@ -304,3 +304,23 @@ def test_capacity_sizes_the_forward_workspace(name):
     assert full - sizes[0] >= (worst - worst // 2) * per_pair
     if d % 8 == 0:   # a shape the backward takes
         assert _lib.layer_backward_workspace_size(dict(c, max_pairs=1000)) == _lib.layer_backward_workspace_size(c)
+
+
+@pytest.mark.parametrize("name", ["vit_b16", "paper_language"])
+def test_fp32_workspaces_add_a_bounded_activations_buffer(name):
+    """An fp32 forward holds its per-pair rows, the pair and slab lists and at
+    most 1 GiB (256 bytes per pair if more) of activations; the backward the
+    activations and their gradients on top of it, and its partial sums in the
+    forward's activations. (Whole activations in both made the backward's
+    workspace of 50,432 tokens, d = 768, K = 16, H = 3072 34.7 GB; it needs
+    23.8 GB without any.)"""
+    c = dict(layer_config(get_config(name)), dtype="f32")
+    N, d, K, B, M = (c[k] for k in ("n_tokens", "d_model", "n_experts", "n_blocks", "block_width"))
+    P, H = N * (K + 1), B * M
+    act = min(4 * H * P, max(1 << 30, 256 * N))
+    lists = 8 * (N * K * B + 64 * (K + 1) * B) + 32 * P + N * (32 + 8 * K) + 4 * -(-N // 64) * (K + 1) * (B + 1)
+    fwd, bwd = _lib.layer_forward_workspace_size(c), _lib.layer_backward_workspace_size(c)
+    assert fwd <= 4 * d * P + act + lists + (4 << 20)
+    small = 8 * B * -(-M // 64) * P + 12 * P + 1024 * (K + 1) * d
+    assert 8 * H * P <= bwd - fwd <= 8 * H * P + max(0, small - act) + 4096
+    assert _lib.layer_forward_workspace_size(dict(c, max_pairs=P // 4)) < fwd

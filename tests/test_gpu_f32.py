@@ -3,7 +3,8 @@ channels or columns, 32 k), against the oracle by the protocols of
 tests/parity.py and tests/test_gpu_backward.py (MI355X only), and the
 workspace-free forward of a layer whose activations do not fit its scratch,
 which runs on the per-pair kernel. A weight that is not finite reaches the
-tokens that run its block and no others."""
+tokens that run its block and no others. Layers whose activations take more
+than 1 GiB run in passes over ranges of experts, blocks or channels."""
 import numpy as np
 import pytest
 
@@ -122,3 +123,60 @@ def test_gradients_past_weights_that_are_not_finite():
     assert not np.any(np.isfinite(got[uses, 7]))
     assert np.all(np.isfinite(got[~uses]))
     assert np.abs(got[~uses] - ref[~uses]).max() <= parity.KERNEL_TOL["f32"] * np.abs(ref).max()
+
+
+# More than 1 GiB of worst-case activations: passes of 33 and 32 experts; of one
+# expert and 4 of 8 blocks; of one expert and 4,096 or 4,095 channels of a block.
+# (tokens, d, K, B, M, every how many tokens one is valid)
+PASSES = {
+    "experts": (3000, 32, 64, 8, 192, 1),
+    "blocks": (20000, 8, 1, 8, 2048, 4),
+    "parts": (40000, 8, 1, 2, 8191, 8),
+}
+
+
+@pytest.mark.parametrize("name", list(PASSES))
+def test_forward_in_passes(name):
+    """The same bits as in one pass, which a capacity of the pairs that the
+    routing needs allows, for the layer and with biases; past weights that are
+    not finite the same values; and the oracle's values."""
+    from paper_2608_10392_amd import _lib
+    n, d, K, B, M, every = PASSES[name]
+    g = generate(get_config("tiny_f32", n_tokens=n, d_model=d, n_experts=K, n_blocks=B, block_width=M, max_shared=B,
+                            mass_mode="topk", fixed_k=min(2, K)))
+    g["valid"] = (np.arange(n) % every == 0).astype(np.uint8)
+    dev, orec, grec, Y = run_case(g, f"fp32 passes {name}", n_sample=64)
+    cfg = layer_config(g["cfg"])
+    pairs = int(g["valid"].sum()) * (1 + min(2, K))
+    one = dict(cfg, max_pairs=pairs)
+    assert 4 * n * (K + 1) * B * M > 1 << 30 > 4 * pairs * B * M
+    f = dict(dtype=torch.float32, device="cuda:0")
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    blk = dict(norm="none", residual=True, ln_eps=1e-6, ln_gamma=None, ln_beta=None,
+               b_up=torch.randn(K + 1, B * M, generator=gen, **f), b_down=torch.randn(K + 1, d, generator=gen, **f))
+    bad = dev.W_down.clone()
+    bad[0, 3, M + 1] = float("nan")
+    bad[min(2, K), 5, M - 1] = float("inf")
+    for W_down, block in ((dev.W_down, None), (dev.W_down, blk), (bad, None)):
+        out = []
+        for c in (cfg, one):
+            y = torch.empty_like(dev.Y)
+            layer = (dev.X, dev.valid, dev.W_router, dev.prototypes, dev.W_up, W_down, y)
+            if block is None:
+                ws = _lib.alloc_workspace(_lib.layer_forward_workspace_size(c))
+                _lib.layer_forward(c, *layer, ws)
+            else:
+                ws = _lib.alloc_workspace(_lib.block_forward_workspace_size(c, block))
+                _lib.block_forward(c, block, *layer, ws)
+            out.append(y)
+        finite = torch.isfinite(out[0])
+        assert torch.equal(finite, torch.isfinite(out[1]))
+        assert bool(finite.all()) == (W_down is dev.W_down)
+        if W_down is dev.W_down:
+            assert torch.equal(out[0], out[1])
+        else:   # rows formed again are summed in another order
+            err = (out[0][finite] - out[1][finite]).abs().max() / out[1][finite].square().mean().sqrt()
+            assert err <= parity.KERNEL_TOL["f32"]
+    assert np.array_equal(Y, dev.output_numpy())
+    del dev, bad, ws
+    torch.cuda.empty_cache()
