@@ -252,14 +252,13 @@ void up_kernel(UpParams p) {
     const int nk = p.d / S::SK;                       // real stages per tile
     const int nst = max(nk, 4);                       // stages per tile, padding included
     const TileQueue tq(p.queue, n_tiles);
-    // ctl[0]: the ticket of the second tile, taken here and read once the
-    // first tile's row lists are in; ctl[1]: that of the tile after next,
+    // ctl[0]: the ticket of the second tile, taken and read with the first
+    // tile's row lists; ctl[1]: that of the tile after next,
     // taken at stage 0 of each tile, written at stage 1, read after stage 2.
     int* ctl = reinterpret_cast<int*>(lds_up + RING + 16 * TM);
     int tile = tq.first();
     if (tile >= tq.hi) return;
     int taken = 0;
-    if (tid == 0) taken = tq.take_second();
 
     // Fragment addresses inside a stage: lane (lr, lh) reads row base + lr,
     // chunk 2 k + lh of k step k; 32-row steps keep the swizzle, so row
@@ -337,7 +336,7 @@ void up_kernel(UpParams p) {
     int par = 0;
     int info = ld_uniform(p.tile_info + tile);
     fetch_rows(ld_uniform(p.tile_rows + tile), 0);
-    if (tid == 0) ctl[0] = taken;
+    if (tid == 0) ctl[0] = tq.take_second();   // its round trip runs beside the lists'
     wait_vmcnt<0>();
     __syncthreads();
     int next = tq.at(__builtin_amdgcn_readfirstlane(ctl[0]));
