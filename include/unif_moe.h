@@ -165,10 +165,11 @@ int32_t unif_moe_route(const unif_moe_config* cfg, const void* X, const uint8_t*
  * host; a capacity max_pairs > 0 sizes the pair-indexed buffers (the fp16
  * activations, the per-expert rows, the pair and slab lists, the down-tile
  * tables) for that many pairs instead, which shrinks the workspace by about
- * N (K+1) / max_pairs for large layers. fp32 layers keep 4 H bytes of
- * activations per pair, but at most 1 GiB (or 256 N bytes, if that is more):
- * layers that need more run the expert FFNs in passes over ranges of experts
- * and, where one expert's do not fit, of its channels, with the same results. */
+ * N (K+1) / max_pairs for large layers. fp32 layers hold the same lists
+ * (8 K B bytes per token) and keep 4 H bytes of activations per pair, but at
+ * most 1 GiB (or 256 N bytes, if that is more): layers that need more run the
+ * expert FFNs in passes over ranges of experts and, where one expert's do not
+ * fit, of its channels, with the same results. */
 int32_t unif_moe_layer_forward_workspace_size(const unif_moe_config* cfg, size_t* bytes);
 
 /* Forward pass of the layer: routing, token permutation, block-sparse expert

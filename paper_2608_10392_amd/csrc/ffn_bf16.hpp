@@ -142,15 +142,18 @@ __host__ __device__ constexpr int down_lds_bytes(int TM, int BN) { return 2 * (T
 // one each by their index, and take the rest in order through counter
 // queue[x]. (Taking the first two tiles from the counter left half of the
 // compute units idle when a call has fewer tiles than twice the workgroups,
-// and put the atomic's round trip before the first copy.) A down queue of at
-// least 2 g tiles gives workgroup i the first two, 2 i and 2 i + 1, instead:
+// and put the atomic's round trip before the first copy.) A down queue of
+// 2 g to 8 g tiles gives workgroup i the first two, 2 i and 2 i + 1, instead:
 // neighbours are column tiles of one row tile, about equally long, and all
 // workgroups' second tiles are known at once anyway (each takes a tile ahead).
 // With single tiles the down-projections of mid-sized calls were up to 8%
 // slower (20,000 tokens of d = 512, K = 16, 8 blocks of 128: 127 us against
 // 118, the call 295 us against 287 with pairs); the up-projection, whose
 // neighbours share token rows rather than a length, is as fast or faster with
-// single tiles (640-wide calls 2 to 4 us). Indices past hi mean "no tile".
+// single tiles (640-wide calls 2 to 4 us). In longer queues the start does not
+// matter (vit_b16, 10 g tiles: the same time), but the pairs read rows of H that
+// single tiles share in L2 (2.30 GB a launch against 1.97). Indices past hi mean
+// "no tile".
 // gridDim.x is a multiple of kXcds.
 struct TileQueue {
     int* ctr;
@@ -174,7 +177,7 @@ struct TileQueue {
         ctr = queue + x;
         lo = ld_uniform(slices + x);
         hi = ld_uniform(slices + x + 1);
-        pairs = hi - lo >= 2 * g;
+        pairs = hi - lo >= 2 * g && hi - lo < 8 * g;
         base = lo + (pairs ? 2 * g : g);
     }
     // The next ticket; one lane only (a vector atomic with return).

@@ -545,7 +545,9 @@ __device__ __forceinline__ void put_logits(float* P, int ls, const f32x4 (&acc)[
 // For few tiles the chain of k steps of one wave sets the time, and this
 // splits it (16,384 tokens of d = 768, K = B = 16: 21 us against 25 us in two
 // launches; d = 1024, K = B = 32: 38 against 46 us); with more tiles the router
-// rows it re-reads per tile make it slower (see kSplitKTiles).
+// rows it re-reads per tile make it slower (see kSplitKTiles). (Routers of 113
+// to 128 columns spill 18 registers in the loop of k steps; 16,000 tokens of
+// d = 1024, K = B = 64 take 72 us.)
 // NCT: 16-column tiles of the bf16 router; 0: fp32 tokens. The
 // last p.cvt_blocks workgroups do the launch's copy job.
 constexpr int kSplitWaves = 4;
@@ -703,7 +705,9 @@ __global__ __launch_bounds__(kSplitWaves * 64) void route_split_k_kernel(RoutePa
 // reads and products of one wave (two workgroups share a compute unit, so
 // registers are the limit: W_shr goes through LDS and only one step's
 // fragments are read ahead; with spills in the loop a stage took 4 us, since
-// every reload waits behind the copies in flight). d = 1024, K = B = 32:
+// every reload waits behind the copies in flight. The nine or ten registers
+// that the kernels of 17 to 64 columns spill now are the decisions', after the
+// loop). d = 1024, K = B = 32:
 // 100,001 tokens 477 us with one fused kernel of 4 tokens per decision pass,
 // 79 us here; 32,768 tokens 71 us with a tile per workgroup, 47 us here.
 // The last p.cvt_blocks workgroups do the launch's copy job.
