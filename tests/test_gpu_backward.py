@@ -71,8 +71,7 @@ CASES = {
                                              block_width=64, max_shared=8)),
     "f32": ("tiny_f32", dict(n_tokens=200, d_model=64, n_experts=4, n_blocks=4, block_width=32,
                              max_shared=4)),
-    # a block width that is not a multiple of the fp32 kernels' 16-channel
-    # steps: a step then spans two blocks
+    # a block width of less than one 32-channel stage of the fp32 kernels
     "f32_m24": ("tiny_f32", dict(n_tokens=200, d_model=64, n_experts=4, n_blocks=4, block_width=24,
                                  max_shared=4)),
     # edge shapes: one token; two blocks of the widest kernel; 64 experts x 64 blocks
