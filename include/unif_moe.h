@@ -378,7 +378,8 @@ int32_t unif_moe_diversity_loss(const unif_moe_config* cfg, const float* W_route
  * Errors: as unif_moe_layer_forward; UNIF_EWORKSPACE when the layer needs
  * more scratch than UNIF_MOE_STATIC_WORKSPACE_BYTES (the size reported by
  * unif_moe_layer_forward_workspace_size; checked on the host before any HIP
- * call); UNIF_EDEVICE when the array's address cannot be obtained. */
+ * call; fp32 layers that fit without activations and row lists run pair by
+ * pair instead, far slower, with sums in another order); UNIF_EDEVICE when the array's address cannot be obtained. */
 int32_t unif_moe_layer_forward_static(const unif_moe_config* cfg, const void* X, const uint8_t* valid,
                                       const float* W_router, const float* prototypes, const void* W_up,
                                       const void* W_down, void* Y, const unif_moe_routing* routing_out,
